@@ -56,16 +56,16 @@ __device__ __forceinline__ float e2m1_value(uint32_t code) {
 // Smallest e in [-127, 127] with 2^e >= s. Non-positive s (and -0) -> -127; +inf -> 127;
 // NaN sets *nan_seen and gives -127.
 __device__ __forceinline__ int e8m0_ceil_exp(float s, bool &nan_seen) {
-    // every case computed, the result selected (no divergent branches)
+    // No divergent branches. For normal s the biased exponent of the next power of two is the exponent
+    // field after adding all mantissa bits but one ulp; s <= 2^-127 (0x00400000; negative s as a signed
+    // integer too) is -127, and a subnormal above that rounds up to 2^-126 by the same addition.
     const uint32_t b = __float_as_uint(s);
     const bool nan = (b & 0x7FFFFFFFu) > 0x7F800000u;
-    const uint32_t E = b >> 23, man = b & 0x7FFFFFu;
-    int e = (int)E - 127 + (man != 0u);
-    e = E == 0u ? (man > 0x400000u ? -126 : -127) : e;  // subnormal s < 2^-126; 2^-127 is man 0x400000
-    e = e > 127 ? 127 : e;
-    e = (nan || (int32_t)b <= 0) ? -127 : e;
+    uint32_t E = (b + 0x7FFFFFu) >> 23;
+    E = E > 254u ? 254u : E;
+    E = (nan || (int32_t)b <= 0x00400000) ? 0u : E;
     nan_seen = nan_seen || nan;
-    return e;
+    return (int)E - 127;
 }
 
 // E8M0 rounded down, the OCP MX rule: e = floor(log2 s) - drop, clamped to [-127, 127] (drop = 2 for an

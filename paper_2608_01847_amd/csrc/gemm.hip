@@ -251,9 +251,10 @@ BwdPlan plan_bwd(int op_dt, int fmt, int sb, int64_t M, int64_t N, int64_t K, bo
         // (one 256 x 256 workgroup per CU on the MFMA path, several 64 x 64 ones on the VALU path):
         // minimise rounds * (steps per split + epilogue), each split keeping >= 4 steps. The MFMA
         // path's straight-through epilogue (a 256 x 256 tile at one wave per SIMD) costs about as
-        // much as 36 of its 64-token steps, as measured on MI355X.
+        // much as 20 of its 64-token steps: of 4 to 36, 16 to 20 gave the best splits on layers of 2,048 to
+        // 65,536 tokens (the others up to 2% slower).
         const int64_t slots = p.path == 1 ? kMfmaConcurrentWgs : 2048;
-        const int64_t epilogue_steps = p.path == 1 ? 36 : 4;
+        const int64_t epilogue_steps = p.path == 1 ? 20 : 4;
         const int64_t max_splits = std::max<int64_t>(1, std::min<int64_t>(steps_total / 4, 4096));
         int64_t best = -1;
         for (int64_t s = 1; s <= max_splits; s++) {
@@ -319,9 +320,11 @@ hipError_t launch_recon_bwd(const BwdPlan &p, int op_dt, int fmt, int sb, int st
     float *part_s = reinterpret_cast<float *>(reinterpret_cast<char *>(ws) + kWsHeader);
     float *part_c = part_s + p.splits * N * nb;
     if (p.path == 1) {
-        hipError_t e = launch_bwd_mfma(fmt, w_dt, dY, X, M, N, K, p.chunk, p.splits, W, s_fp, c, sb,
-                                       alpha, ste_clip, e8m0_floor, part_s, part_c, flag, st);
-        if (e != hipSuccess) return e;
+        // one split: the kernel writes the gradients, nothing is left to sum
+        const int direct = p.splits == 1;
+        hipError_t e = launch_bwd_mfma(fmt, w_dt, dY, X, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, alpha, ste_clip,
+                                       e8m0_floor, direct ? grad_s : part_s, direct ? grad_c : part_c, direct, flag, st);
+        if (e != hipSuccess || direct) return e;
     } else {
         dim3 grid((unsigned)cdiv(K, 64), (unsigned)cdiv(N, 64), (unsigned)p.splits);
 #define BV(D, F, WD) bwd_valu_kernel<D, F, WD><<<grid, 256, 0, st>>>(dY, X, M, N, K, p.chunk, W, s_fp, c, sb, alpha, ste_clip, e8m0_floor, part_s, part_c, G_out, flag)
@@ -349,9 +352,10 @@ hipError_t launch_recon_bwd_mx(const BwdPlan &p, int sb, int ste_clip, int e8m0_
     const int64_t nb = K / 32, ns = K / sb;
     float *part_s = reinterpret_cast<float *>(reinterpret_cast<char *>(ws) + kWsHeader);
     float *part_c = part_s + p.splits * N * nb;
-    hipError_t e = launch_bwd_mfma_mx(w_dt, dY, Xc, Xs, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, ste_clip,
-                                      e8m0_floor, part_s, part_c, flag, st);
-    if (e != hipSuccess) return e;
+    const int direct = p.splits == 1;  // the kernel writes the gradients, nothing is left to sum
+    hipError_t e = launch_bwd_mfma_mx(w_dt, dY, Xc, Xs, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, ste_clip, e8m0_floor,
+                                      direct ? grad_s : part_s, direct ? grad_c : part_c, direct, flag, st);
+    if (e != hipSuccess || direct) return e;
     const int64_t total = N * (nb + ns);
     const unsigned g = (unsigned)std::min<int64_t>(std::max<int64_t>(cdiv(total, 256), 1), kStreamGridCap);
     bwd_finish_kernel<<<g, 256, 0, st>>>(part_s, part_c, p.splits, N * nb, N * ns, c, nullptr, kFmtMX, grad_s, grad_c);

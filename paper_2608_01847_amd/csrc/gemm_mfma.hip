@@ -648,164 +648,225 @@ fwd_mfma_kernel(const void *__restrict__ X, const void *__restrict__ W, const ui
     if (n0 + t < N) colpart[(int64_t)tm * N + n0 + t] = red[t] + red[kTile + t];
 }
 
+// the value of lane l ^ X (X = 1 or 2), a DPP move within each four lanes
+template <int X>
+__device__ __forceinline__ float quad_xor(float v) {
+    constexpr int kCtrl = X == 1 ? 0xB1 : 0x4E;  // quad_perm [1, 0, 3, 2] / [2, 3, 0, 1]
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), kCtrl, 0xF, 0xF, true));
+}
+
 // Fused straight-through epilogue of the backward kernels on G^T = acc (a 256 k x 256 n tile):
-// per-split partial sums of G m w per sub-block and of G (q - m u) per block.
+// per-split partial sums of G m w per sub-block and of G (q - m u) per block or, where the token range
+// is not split (`direct`), the gradients themselves.
 // acc[i][j][r] is G[n][k] for n = n0 + 128 wn + 32 j + (lane % 32) and
-// k = k0 + 128 wm + 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4: lane l holds, for each group g of
-// 8 k, the 4 consecutive k 4 (l / 32) .. + 3, and lanes l, l ^ 32 together hold the whole group.
-template <int FMT, int WDT>
-__device__ __forceinline__ void ste_epilogue(const f32x16_t (&acc)[4][4], int64_t k0, int64_t n0, int64_t split,
-                                             int64_t N, int64_t K, const void *__restrict__ W,
-                                             const float *__restrict__ s_fp, const float *__restrict__ c, int sb_log2,
-                                             const float *__restrict__ alpha_ptr, int ste_clip, int e8m0_floor,
-                                             float *__restrict__ part_s, float *__restrict__ part_c, uint32_t *flag,
-                                             int wm, int wn, int lane) {
+// k = k0 + 128 wm + 32 i + 8 (r / 4) + 4 (lane / 32) + r % 4.
+//
+// Bound by vector instructions (one wave per SIMD, 256 elements per lane). G goes through LDS a quarter
+// (accumulator column j, 64 rows n x 256 k, 64 KB, two buffers) at a time, so that a thread then holds 8
+// consecutive k of one row, as in the streaming fake-quant kernels: one scale, one coefficient and one
+// division per 8 elements (u by div_by_scale where the whole wave's operands are in its range), 16-byte
+// loads of W and 128-byte runs of c and of the sums, and the quarters run as a loop, whose code stays in
+// the instruction cache. An epilogue in the accumulator layout (a lane holding 4 k of 32 rows, a true
+// division per element, all 256 elements unrolled, 8- and 4-byte accesses 32 rows apart) made the whole
+// backward of 2,048 x 1,024 x 2,560 (packed) take 65.4 us instead of 39.8, that of 3,001 x 1,368 x 2,128
+// (NVFP4) 72.8 instead of 46.6 and that of 4,096 x 32,000 x 2,560 703 instead of 574.
+template <int FMT, int WDT, int NCOEF>
+__device__ __forceinline__ void ste_epilogue_n(const f32x16_t (&acc)[4][4], int64_t k0, int64_t n0, int64_t split,
+                                               int64_t N, int64_t K, const void *__restrict__ W,
+                                               const float *__restrict__ s_fp, const float *__restrict__ c, int sb_log2,
+                                               const float *__restrict__ alpha_ptr, int ste_clip, int e8m0_floor,
+                                               float *__restrict__ part_s, float *__restrict__ part_c, int direct,
+                                               uint32_t *flag, char *smem) {
     constexpr int B = block_of(FMT);
-    constexpr int NBI = 32 / B;                   // blocks per 32 k (1 MXFP4, 2 NVFP4)
     constexpr int WB = WDT == kBF16 ? 2 : 4;      // bytes per weight element
-    const float alpha = FMT == kFmtNV ? *alpha_ptr : 1.0f;
-    const int sb = 1 << sb_log2;
-    const int64_t nb = K / B, ns = K >> sb_log2;
+    constexpr int EPC = 8 / NCOEF;                // elements per coefficient within a thread's 8
+    constexpr int kItems = 8;                     // 8-element pieces per thread and quarter
+    constexpr int kWords = WB * 8 / 16;           // 16-byte words of W per piece
+    constexpr uint32_t kQuarter = 64u * 1024u;
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int lr = lane & 31, lh = lane >> 5;
+    const float alpha = FMT == kFmtNV ? *alpha_ptr : 1.0f;
+    const float lim = ste_clip ? 6.0f : __builtin_inff();
+    const int64_t nb = K / B, ns = K >> sb_log2;
     const bool has_c = c != nullptr;
     bool bad = false;
-    // W, S_fp and c of the tile's rows come through range-checked buffer loads: rows past N read
-    // as zeros, and so do columns past K (bit 31 of the offset). Out-of-range elements have G = 0
-    // and w = 0 and add exactly zero to every sum; they are kept out of the domain check, and
-    // their partial sums are not stored (bit 31 again: the store is dropped). All offsets are
-    // 32-bit: a tile spans 256 rows of W (checked when the path is chosen).
+    // W, S_fp and c of the tile's rows come through range-checked buffer loads: rows past N read as zeros,
+    // and so do columns past K (bit 31 of the offset); both are kept out of the domain check, and their
+    // sums are not stored (bit 31 again: the store is dropped). All offsets are 32-bit: a tile spans 256
+    // rows of W (checked when the path is chosen), so none below bit 31 carries into or past it.
     const __amdgpu_buffer_rsrc_t rw = make_rsrc(reinterpret_cast<const char *>(W) + n0 * K * WB, (N - n0) * K * WB);
     const __amdgpu_buffer_rsrc_t rsf = make_rsrc(s_fp + n0 * nb, (N - n0) * nb * 4);
     const __amdgpu_buffer_rsrc_t rc = make_rsrc(has_c ? c + n0 * ns : s_fp, has_c ? (N - n0) * ns * 4 : 0);
     const __amdgpu_buffer_rsrc_t rps = make_rsrc(part_s + (split * N + n0) * nb, (N - n0) * nb * 4);
     const __amdgpu_buffer_rsrc_t rpc = make_rsrc(part_c + (split * N + n0) * ns, (N - n0) * ns * 4);
     const uint32_t K32 = (uint32_t)K, nb32 = (uint32_t)nb, ns32 = (uint32_t)ns;
-    auto past = [&](uint32_t k) { return (uint32_t)(k >= K32) << 31; };  // k < 2^31 (K is)
-    const uint32_t lh_drop = (uint32_t)lh << 31;  // stores made by the lane pair's lower lane only
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    static_for<4>([&](auto j) {
-        const uint32_t nl = wn * 128 + j * 32 + lr;  // row of W inside the tile (< 256)
-        const bool n_ok = n0 + nl < N;
-        const uint32_t n_drop = (uint32_t)!n_ok << 31;
-        // all loads of this column first
-        float wv[4][4][4];   // [i][g][e]
-        float sv[4][NBI];    // [i][block]
-        float cv[4][4][2];   // [i][g][elements 0-1 / 2-3]
-        static_for<4>([&](auto i) {
-            const uint32_t kb = (uint32_t)k0 + wm * 128 + i * 32;
-            static_for<4>([&](auto g) {
-                const uint32_t k = kb + 8 * g + 4 * lh;  // this lane's 4 consecutive k
-                const uint32_t wo = ((nl * K32 + k) * WB) | past(k);
-                if constexpr (WDT == kBF16) {
-                    const u32x2 p = __builtin_amdgcn_raw_buffer_load_b64(rw, (int)wo, 0, 0);
-                    wv[i][g][0] = __uint_as_float(p.x << 16);
-                    wv[i][g][1] = __uint_as_float(p.x & 0xFFFF0000u);
-                    wv[i][g][2] = __uint_as_float(p.y << 16);
-                    wv[i][g][3] = __uint_as_float(p.y & 0xFFFF0000u);
-                } else {
-                    const u32x4 p = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)wo, 0, 0);
-                    wv[i][g][0] = __uint_as_float(p.x);
-                    wv[i][g][1] = __uint_as_float(p.y);
-                    wv[i][g][2] = __uint_as_float(p.z);
-                    wv[i][g][3] = __uint_as_float(p.w);
+    const uint32_t rows = N - n0 < kTile ? (uint32_t)(N - n0) : (uint32_t)kTile;
+    // This thread's pieces of quarter q: k = kl .. kl + 7 of local rows r0 + 8 i (i = 0..7), which are rows
+    // r0 + row_base(i, q) of the tile (local row rl is tile row 128 (rl / 32) + 32 q + rl % 32).
+    const uint32_t kl = (uint32_t)k0 + 8u * ((uint32_t)t & 31u), r0 = (uint32_t)t >> 5;
+    const bool k_ok = kl < K32;
+    const uint32_t past = (uint32_t)!k_ok << 31;  // K < 2^31
+    auto row_base = [](uint32_t i, uint32_t q) { return (i >> 2) * 128u + q * 32u + 8u * (i & 3u); };
+    const uint32_t w_off = (r0 * K32 * WB + kl * WB) | past, s_off = (r0 * nb32 + kl / B) * 4u | past,
+                   c_off = (r0 * ns32 + (kl >> sb_log2)) * 4u | past;
+    // stores of a sum over several threads are made by the first of them
+    const uint32_t s_st = s_off | ((kl & (uint32_t)(B - 1)) ? 0x80000000u : 0u);
+    const uint32_t c_st = c_off | (NCOEF == 1 && (kl & ((1u << sb_log2) - 1u)) ? 0x80000000u : 0u);
+    u32x4 raw[kItems][kWords];
+    float sv[kItems], cv[kItems][NCOEF];
+    auto load_item = [&](auto i, uint32_t q) {
+        const uint32_t rb = row_base(i, q);
+#pragma unroll
+        for (int h = 0; h < kWords; h++)
+            raw[i][h] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(w_off + rb * K32 * WB + 16u * h), 0, 0);
+        sv[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsf, (int)(s_off + rb * nb32 * 4u), 0, 0));
+#pragma unroll
+        for (int k = 0; k < NCOEF; k++)
+            cv[i][k] = __uint_as_float(
+                __builtin_amdgcn_raw_buffer_load_b32(rc, (int)(c_off + rb * ns32 * 4u + 4u * k), 0, 0));
+    };
+    static_for<kItems>([&](auto i) { load_item(i, 0u); });
+    // 16-byte chunk ch (4 k) of local row rl lies at rl 1024 + 16 (ch ^ rl % 32): the xor spreads one chunk of
+    // 32 rows (the writes) and the chunks of one row (the reads) over the banks
+    const uint32_t wr = ((uint32_t)wn * 32u + lr) * 1024u + (((uint32_t)wm * 32u + lh) ^ (uint32_t)lr) * 16u;
+    uint32_t rd[4];  // chunk 2 (t % 32) of row r0 + 8 i, i = 0..3; the next chunk is at rd ^ 16
+#pragma unroll
+    for (uint32_t i = 0; i < 4; i++) rd[i] = (r0 + 8u * i) * 1024u + ((2u * ((uint32_t)t & 31u)) ^ (r0 + 8u * i)) * 16u;
+    __syncthreads();  // every wave is done with the operand stages
+#pragma nounroll
+    for (uint32_t q = 0; q < 4u; q++) {
+        char *const buf = smem + (q & 1u) * kQuarter;
+        auto put = [&](auto j) {
+            static_for<16>([&](auto ig) {
+                constexpr int i = ig / 4, g = ig % 4;
+                const f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+                *reinterpret_cast<f32x4 *>(buf + (wr ^ (16u * (8u * i + 2u * g)))) = v;
+            });
+        };
+        if (q == 0u) put(std::integral_constant<int, 0>{});
+        else if (q == 1u) put(std::integral_constant<int, 1>{});
+        else if (q == 2u) put(std::integral_constant<int, 2>{});
+        else put(std::integral_constant<int, 3>{});
+        // LDS only: the loads of W, s and c stay in flight. A buffer is written again two quarters later,
+        // after the barrier that follows this quarter's reads.
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        f32x4 gv[2][2];  // G of this piece and of the next
+        auto get = [&](auto i) {
+            gv[i & 1][0] = *reinterpret_cast<const f32x4 *>(buf + rd[i & 3] + (i >> 2) * 32768u);
+            gv[i & 1][1] = *reinterpret_cast<const f32x4 *>(buf + (rd[i & 3] ^ 16u) + (i >> 2) * 32768u);
+        };
+        get(std::integral_constant<int, 0>{});
+        static_for<kItems>([&](auto i) {
+            const uint32_t rb = row_base(i, q);
+            const bool ok = k_ok && r0 + rb < rows;
+            if constexpr (i + 1 < kItems) get(std::integral_constant<int, i + 1>{});
+            float g[8], w[8];
+#pragma unroll
+            for (int e = 0; e < 8; e++) g[e] = gv[i & 1][e / 4][e % 4];
+            bool fast;
+            if constexpr (WDT == kBF16) {
+                const uint4 p = make_uint4(raw[i][0].x, raw[i][0].y, raw[i][0].z, raw[i][0].w);
+                fast = bf16x8_over_2p80(p) == 0u;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    w[2 * e] = __uint_as_float(raw[i][0][e] << 16);
+                    w[2 * e + 1] = __uint_as_float(raw[i][0][e] & 0xFFFF0000u);
                 }
-                // coefficients of elements 0-1 and 2-3 (the same sub-block unless sb == 2); without
-                // c the resource is empty and the select makes them 1
-                const uint32_t c0 = ((nl * ns32 + (k >> sb_log2)) * 4u) | past(k);
-                const float l0 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc, (int)c0, 0, 0));
-                float l1 = l0;  // a sub-block of 4 or more holds all four k (sb_log2 is uniform)
-                if (sb_log2 == 1) {
-                    const uint32_t c1 = ((nl * ns32 + ((k + 2) >> sb_log2)) * 4u) | past(k);
-                    l1 = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc, (int)c1, 0, 0));
+            } else {
+                uint32_t top = 0u;  // magnitudes as integers order like the values, NaN above all of them
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const uint32_t b = raw[i][e / 4][e % 4];
+                    w[e] = __uint_as_float(b);
+                    top = std::max(top, b & 0x7FFFFFFFu);
                 }
-                cv[i][g][0] = has_c ? l0 : 1.0f;
-                cv[i][g][1] = has_c ? l1 : 1.0f;
-            });
-            static_for<NBI>([&](auto h) {
-                const uint32_t kh = kb + h * B;
-                const uint32_t so = ((nl * nb32 + kh / B) * 4u) | past(kh);
-                sv[i][h] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsf, (int)so, 0, 0));
-            });
-        });
-        static_for<4>([&](auto i) {
-            const uint32_t kb = (uint32_t)k0 + wm * 128 + i * 32;  // one MXFP4 / two NVFP4 blocks
-            float sdq[NBI];
-            static_for<NBI>([&](auto h) {
-                bool nan = false;
-                uint32_t byte;
-                sdq[h] = weight_sdq(FMT, sv[i][h], alpha, e8m0_floor, byte, nan);
-                bad = bad || (n_ok && kb + h * B < K32 && nan);
-            });
-            float tc[4][2];  // per group of 8 k: this lane's sums of G m w over elements 0-1 / 2-3
-            float ts[4];     // per group of 8 k: this lane's sum of G (q - m u)
-            static_for<4>([&](auto g) {
-                const float sd = sdq[(8 * g) / B];
-                const float cv0 = cv[i][g][0], cv1 = cv[i][g][1];
-                bad = bad || (n_ok && kb + 8 * g < K32 && has_c && (bad_coeff(cv0) || bad_coeff(cv1)));
-                tc[g][0] = tc[g][1] = ts[g] = 0.0f;
-                static_for<4>([&](auto e) {
+                fast = top <= 0x67800000u;  // 2^80
+            }
+            uint32_t byte;
+            bool nan = false;
+            const float sdq = weight_sdq(FMT, sv[i], alpha, e8m0_floor, byte, nan);
+            float cw[NCOEF], sq[NCOEF];
+#pragma unroll
+            for (int k = 0; k < NCOEF; k++) {
+                cw[k] = has_c ? cv[i][k] : 1.0f;
+                nan = nan || bad_coeff(cw[k]);
+                sq[k] = sdq * cw[k];
+                fast = fast && scale_in_fast_range(sq[k]);
+            }
+            bad = bad || (ok && nan);
+            if (q < 3u) load_item(i, q + 1u);  // the next quarter's piece, into the registers just read
+            float tc[NCOEF], ts = 0.0f;  // sums of G m w per sub-block and of G (q - m u)
+#pragma unroll
+            for (int k = 0; k < NCOEF; k++) tc[k] = 0.0f;
+            if (__builtin_expect(__all(fast || !ok), 1)) {
+                // (a piece outside the tensor may divide by zero here; nothing of it is stored, and the other
+                // pieces of its block lie outside too)
+                float u[8], qv[8];
+#pragma unroll
+                for (int k = 0; k < NCOEF; k++) {
+                    const float y = 1.0f / sq[k];
+#pragma unroll
+                    for (int e = k * EPC; e < (k + 1) * EPC; e++) u[e] = div_by_scale(w[e], sq[k], y);
+                }
+                uint32_t p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, u[0], u[1], 1.0f, 0);
+                p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, u[2], u[3], 1.0f, 1);
+                p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, u[4], u[5], 1.0f, 2);
+                p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, u[6], u[7], 1.0f, 3);
+                e2m1_value2<0>(p, qv[0], qv[1]);
+                e2m1_value2<1>(p, qv[2], qv[3]);
+                e2m1_value2<2>(p, qv[4], qv[5]);
+                e2m1_value2<3>(p, qv[6], qv[7]);
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const bool m = __builtin_fabsf(u[e]) <= lim;
+                    tc[e / EPC] = __builtin_fmaf(g[e], m ? w[e] : 0.0f, tc[e / EPC]);
+                    ts = __builtin_fmaf(g[e], qv[e] - (m ? u[e] : 0.0f), ts);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
                     float a1, a2;
-                    ste_terms(acc[i][j][(int)(4 * g + e)], wv[i][g][e], sd, e < 2 ? cv0 : cv1, ste_clip != 0, a1, a2);
-                    tc[g][e >> 1] += a1;
-                    ts[g] += a2;
-                });
-            });
-            // ---- sub-block sums of G m w (scaled by -1/c^2 after the split reduction) ----
-            if (sb <= 4) {
-                // a sub-block lies inside one lane's 4 consecutive k
-                static_for<4>([&](auto g) {
-                    const uint32_t k = kb + 8 * g + 4 * lh;
-                    const uint32_t drop = n_drop | past(k);
-                    if (sb == 4) {
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(tc[g][0] + tc[g][1]), rpc,
-                                                              (int)(((nl * ns32 + (k >> 2)) * 4u) | drop), 0, 0);
-                    } else {
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(tc[g][0]), rpc,
-                                                              (int)(((nl * ns32 + (k >> 1)) * 4u) | drop), 0, 0);
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(tc[g][1]), rpc,
-                                                              (int)(((nl * ns32 + (k >> 1) + 1) * 4u) | drop), 0, 0);
-                    }
-                });
-            } else {
-                float s8[4];
-                static_for<4>([&](auto g) {
-                    s8[g] = tc[g][0] + tc[g][1];
-                    s8[g] += __shfl_xor(s8[g], 32, 64);
-                });
-                const uint32_t drop = n_drop | lh_drop;
-                if (sb == 8) {
-                    static_for<4>([&](auto g) {
-                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s8[g]), rpc,
-                                                              (int)(((nl * ns32 + (kb >> 3) + g) * 4u) | drop | past(kb + 8 * g)), 0, 0);
-                    });
-                } else if (sb == 16) {
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s8[0] + s8[1]), rpc,
-                                                          (int)(((nl * ns32 + (kb >> 4)) * 4u) | drop | past(kb)), 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(s8[2] + s8[3]), rpc,
-                                                          (int)(((nl * ns32 + (kb >> 4) + 1) * 4u) | drop | past(kb + 16)), 0, 0);
-                } else {
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((s8[0] + s8[1]) + (s8[2] + s8[3])), rpc,
-                                                          (int)(((nl * ns32 + (kb >> 5)) * 4u) | drop | past(kb)), 0, 0);
+                    ste_terms(g[e], w[e], sdq, cw[e / EPC], ste_clip != 0, a1, a2);
+                    tc[e / EPC] += a1;
+                    ts += a2;
                 }
             }
-            // ---- block sums of G (q - m u) ----
-            float h0 = ts[0] + ts[1], h1 = ts[2] + ts[3];
-            h0 += __shfl_xor(h0, 32, 64);
-            h1 += __shfl_xor(h1, 32, 64);
-            const uint32_t drop = n_drop | lh_drop;
-            if constexpr (B == 32) {
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(h0 + h1), rps,
-                                                      (int)(((nl * nb32 + (kb >> 5)) * 4u) | drop | past(kb)), 0, 0);
-            } else {
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(h0), rps,
-                                                      (int)(((nl * nb32 + (kb >> 4)) * 4u) | drop | past(kb)), 0, 0);
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(h1), rps,
-                                                      (int)(((nl * nb32 + (kb >> 4) + 1) * 4u) | drop | past(kb + 16)), 0, 0);
+            const uint32_t drop = ok ? 0u : 0x80000000u;
+            if constexpr (NCOEF == 1) {
+                if (sb_log2 >= 4) tc[0] += quad_xor<1>(tc[0]);
+                if (sb_log2 >= 5) tc[0] += quad_xor<2>(tc[0]);
             }
+#pragma unroll
+            for (int k = 0; k < NCOEF; k++) {
+                if (direct) tc[k] = -tc[k] / (cw[k] * cw[k]);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(tc[k]), rpc,
+                                                      (int)((c_st + rb * ns32 * 4u + 4u * k) | drop), 0, 0);
+            }
+            ts += quad_xor<1>(ts);
+            if (B == 32) ts += quad_xor<2>(ts);
+            if (FMT == kFmtNV && direct) ts *= alpha;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(ts), rps, (int)((s_st + rb * nb32 * 4u) | drop), 0, 0);
         });
-    });
+    }
     if (bad) raise_domain_flag(flag);
+}
+
+template <int FMT, int WDT>
+__device__ __forceinline__ void ste_epilogue(const f32x16_t (&acc)[4][4], int64_t k0, int64_t n0, int64_t split,
+                                             int64_t N, int64_t K, const void *__restrict__ W,
+                                             const float *__restrict__ s_fp, const float *__restrict__ c, int sb_log2,
+                                             const float *__restrict__ alpha_ptr, int ste_clip, int e8m0_floor,
+                                             float *__restrict__ part_s, float *__restrict__ part_c, int direct,
+                                             uint32_t *flag, char *smem) {
+    auto go = [&](auto nc) {
+        ste_epilogue_n<FMT, WDT, decltype(nc)::value>(acc, k0, n0, split, N, K, W, s_fp, c, sb_log2, alpha_ptr, ste_clip,
+                                                      e8m0_floor, part_s, part_c, direct, flag, smem);
+    };
+    if (sb_log2 >= 3) go(std::integral_constant<int, 1>{});  // coefficients per 8 elements
+    else if (sb_log2 == 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 4>{});
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -814,7 +875,8 @@ __global__ void __launch_bounds__(kThreads, 1)
 bwd_mfma_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ X, int64_t M, int64_t N, int64_t K,
                 int64_t chunk, const void *__restrict__ W, const float *__restrict__ s_fp,
                 const float *__restrict__ c, int sb_log2, const float *__restrict__ alpha_ptr, int ste_clip,
-                int e8m0_floor, float *__restrict__ part_s, float *__restrict__ part_c, uint32_t *flag, int tiles_n) {
+                int e8m0_floor, float *__restrict__ part_s, float *__restrict__ part_c, int direct, uint32_t *flag,
+                int tiles_n) {
     __shared__ __attribute__((aligned(16))) char smem[kBwdStages * kBwdStageBytes];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     // linear id -> (split, tile): splits outermost, tiles of one split in grouped order, so that an
@@ -905,8 +967,9 @@ bwd_mfma_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ X,
     tr_wait(f);  // no read may still be in flight when the workgroup ends
     // the empty slots' zero writes must land before the workgroup's LDS is handed on
     FOCUS_WAIT_VMCNT(0);
+    static_assert(sizeof(smem) >= 128 * 1024, "the epilogue's two quarters fit");
     ste_epilogue<FMT, WDT>(acc, k0, n0, split, N, K, W, s_fp, c, sb_log2, alpha_ptr, ste_clip, e8m0_floor, part_s,
-                           part_c, flag, wm, wn, lane);
+                           part_c, direct, flag, smem);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -995,7 +1058,7 @@ __global__ void __launch_bounds__(kThreads, 1)
 bwd_mfma_mx_kernel(const uint16_t *__restrict__ dY, const uint8_t *__restrict__ Xc, const uint8_t *__restrict__ Xs,
                    int64_t M, int64_t N, int64_t K, int64_t chunk, const void *__restrict__ W,
                    const float *__restrict__ s_fp, const float *__restrict__ c, int sb_log2, int ste_clip,
-                   int e8m0_floor, float *__restrict__ part_s, float *__restrict__ part_c, uint32_t *flag,
+                   int e8m0_floor, float *__restrict__ part_s, float *__restrict__ part_c, int direct, uint32_t *flag,
                    int tiles_n) {
     __shared__ __attribute__((aligned(16))) char smem[kMxLdsBytes];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
@@ -1189,8 +1252,9 @@ bwd_mfma_mx_kernel(const uint16_t *__restrict__ dY, const uint8_t *__restrict__ 
     if (kt + 1 < nk) step(kt + 1, h, f, g);
     tr_wait(f);  // no read may still be in flight when the workgroup ends
     FOCUS_WAIT_VMCNT(0);
+    static_assert(sizeof(smem) >= 128 * 1024, "the epilogue's two quarters fit");
     ste_epilogue<kFmtMX, WDT>(acc, k0, n0, split, N, K, W, s_fp, c, sb_log2, nullptr, ste_clip, e8m0_floor, part_s,
-                              part_c, flag, wm, wn, lane);
+                              part_c, direct, flag, smem);
 }
 
 // ================================================================================================
@@ -1246,7 +1310,7 @@ bool mfma_bwd_mx_supported(int64_t M, int64_t N, int64_t K) {
 hipError_t launch_bwd_mfma_mx(int w_dt, const void *dY, const void *Xc, const void *Xs, int64_t M, int64_t N,
                               int64_t K, int64_t chunk, int64_t splits, const void *W, const float *s_fp,
                               const float *c, int sb, int ste_clip, int e8m0_floor, float *part_s, float *part_c,
-                              uint32_t *flag, hipStream_t st) {
+                              int direct, uint32_t *flag, hipStream_t st) {
     const int tiles_k = (int)((K + kTile - 1) / kTile), tiles_n = (int)((N + kTile - 1) / kTile);
     int sbl = 0;
     while ((1 << sbl) < sb) sbl++;
@@ -1255,23 +1319,23 @@ hipError_t launch_bwd_mfma_mx(int w_dt, const void *dY, const void *Xc, const vo
     const uint8_t *xc = static_cast<const uint8_t *>(Xc), *xs = static_cast<const uint8_t *>(Xs);
     if (w_dt == kBF16)
         bwd_mfma_mx_kernel<kBF16><<<grid, kThreads, 0, st>>>(dy, xc, xs, M, N, K, chunk, W, s_fp, c, sbl, ste_clip,
-                                                             e8m0_floor, part_s, part_c, flag, tiles_n);
+                                                             e8m0_floor, part_s, part_c, direct, flag, tiles_n);
     else
         bwd_mfma_mx_kernel<kF32><<<grid, kThreads, 0, st>>>(dy, xc, xs, M, N, K, chunk, W, s_fp, c, sbl, ste_clip,
-                                                            e8m0_floor, part_s, part_c, flag, tiles_n);
+                                                            e8m0_floor, part_s, part_c, direct, flag, tiles_n);
     return hipGetLastError();
 }
 
 hipError_t launch_bwd_mfma(int fmt, int w_dt, const void *dY, const void *X, int64_t M, int64_t N, int64_t K,
                            int64_t chunk, int64_t splits, const void *W, const float *s_fp, const float *c, int sb,
                            const float *alpha, int ste_clip, int e8m0_floor, float *part_s, float *part_c,
-                           uint32_t *flag, hipStream_t st) {
+                           int direct, uint32_t *flag, hipStream_t st) {
     const int tiles_k = (int)((K + kTile - 1) / kTile), tiles_n = (int)((N + kTile - 1) / kTile);
     int sbl = 0;
     while ((1 << sbl) < sb) sbl++;
     const dim3 grid((unsigned)tiles_k * tiles_n, (unsigned)splits);
     const uint16_t *dy = static_cast<const uint16_t *>(dY), *x = static_cast<const uint16_t *>(X);
-#define BM(F, WD) bwd_mfma_kernel<F, WD><<<grid, kThreads, 0, st>>>(dy, x, M, N, K, chunk, W, s_fp, c, sbl, alpha, ste_clip, e8m0_floor, part_s, part_c, flag, tiles_n)
+#define BM(F, WD) bwd_mfma_kernel<F, WD><<<grid, kThreads, 0, st>>>(dy, x, M, N, K, chunk, W, s_fp, c, sbl, alpha, ste_clip, e8m0_floor, part_s, part_c, direct, flag, tiles_n)
     if (fmt == kFmtMX) { if (w_dt == kBF16) BM(kFmtMX, kBF16); else BM(kFmtMX, kF32); }
     else { if (w_dt == kBF16) BM(kFmtNV, kBF16); else BM(kFmtNV, kF32); }
 #undef BM
