@@ -395,7 +395,7 @@ def main():
     achieved = per_launch_flops / (d["avg_ms"] * 1e-3) / 1e12
     src_hash = kernel_source_hash()
     if esz == 4:
-        kname = {"recon_gemm_fwd": "fwd_valu_kernel", "recon_gemm_bwd": "bwd_valu_kernel"}[dominant]
+        kname = {"recon_gemm_fwd": "fwd_f32_kernel", "recon_gemm_bwd": "bwd_f32_kernel"}[dominant]
     else:
         kname = {"recon_gemm_fwd": "fwd_mfma_kernel_mx" if mx_fwd else "fwd_mfma_kernel",
                  "recon_gemm_bwd": "bwd_mfma_mx_kernel" if mx_fwd else "bwd_mfma_kernel"}[dominant]

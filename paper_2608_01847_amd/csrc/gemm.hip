@@ -1,6 +1,6 @@
-// Reconstruction GEMMs of the FOCUS step: planning, the LDS-tiled VALU kernels (fp32 operands,
-// and any shape) with the fused MSE / straight-through epilogues, and the deterministic
-// reductions that finish both. The bf16 MFMA kernels live in gemm_mfma.hip.
+// Reconstruction GEMMs of the FOCUS step: planning, the LDS-tiled VALU kernels (shapes that the MFMA
+// kernels do not take) with the fused MSE / straight-through epilogues, and the deterministic
+// reductions that finish both. The bf16 and fp32 MFMA kernels live in gemm_mfma.hip and gemm_f32.hip.
 #include "focus_device.h"
 #include "gemm_common.h"
 #include "internal.h"
@@ -231,31 +231,37 @@ static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 FwdPlan plan_fwd(int op_dt, int64_t M, int64_t N, int64_t K) {
     FwdPlan p;
-    p.path = (op_dt == kBF16 && mfma_fwd_supported(M, N, K)) ? 1 : 0;
-    const int64_t tm = p.path == 1 ? kMfmaTileM : 64;
-    p.mtiles = cdiv(M, tm);
+    p.path = op_dt == kBF16 ? (mfma_fwd_supported(M, N, K) ? 1 : 0) : (f32_fwd_supported(M, N, K) ? 2 : 0);
+    // fp32: 64 x 64 tiles where they give every CU one, else 32 x 32 with K split over the waves (128 x 256 x
+    // 256 has 8 of the former and 32 of the latter)
+    const bool small = p.path == 2 && cdiv(M, kF32Tile) * cdiv(N, kF32Tile) < kMfmaConcurrentWgs;
+    p.tile_m = p.path == 1 ? kMfmaTileM : (small ? kF32Tile / 2 : 64);
+    p.mtiles = cdiv(M, p.tile_m);
     p.ws_bytes = kWsHeader + (size_t)(p.mtiles * N + N) * sizeof(double);
     return p;
 }
 
 BwdPlan plan_bwd(int op_dt, int fmt, int sb, int64_t M, int64_t N, int64_t K, bool want_G) {
     BwdPlan p;
-    p.path = (op_dt == kBF16 && !want_G && mfma_bwd_supported(M, N, K)) ? 1 : 0;
+    p.path = op_dt == kBF16 ? (!want_G && mfma_bwd_supported(M, N, K) ? 1 : 0) : (f32_bwd_supported(M, N, K) ? 2 : 0);
     const int64_t tn = p.path == 1 ? kMfmaTileN : 64, tk = p.path == 1 ? kMfmaTileK : 64;
-    const int64_t step = p.path == 1 ? kMfmaTokenStep : 16;
+    const int64_t step = p.path == 1 ? kMfmaTokenStep : (p.path == 2 ? kF32TokenStep : 16);
     const int64_t tiles = cdiv(N, tn) * cdiv(K, tk);
     const int64_t steps_total = cdiv(std::max<int64_t>(M, 1), step);
     int64_t splits = 1;
     if (!want_G) {
         // The token range is split so that tiles * splits workgroups fill the chip in whole rounds
         // (one 256 x 256 workgroup per CU on the MFMA path, several 64 x 64 ones on the VALU path):
-        // minimise rounds * (steps per split + epilogue), each split keeping >= 4 steps. The MFMA
+        // minimise rounds * (steps per split + epilogue), each split keeping >= 4 steps (fp32: 1). The MFMA
         // path's straight-through epilogue (a 256 x 256 tile at one wave per SIMD) costs about as
         // much as 20 of its 64-token steps: of 4 to 36, 16 to 20 gave the best splits on layers of 2,048 to
         // 65,536 tokens (the others up to 2% slower).
-        const int64_t slots = p.path == 1 ? kMfmaConcurrentWgs : 2048;
-        const int64_t epilogue_steps = p.path == 1 ? 20 : 4;
-        const int64_t max_splits = std::max<int64_t>(1, std::min<int64_t>(steps_total / 4, 4096));
+        // On the fp32 path a CU's matrix units are busy with one workgroup, so workgroups queue per CU too;
+        // its epilogue (64 x 64) costs about 3 of its 32-token steps.
+        const int64_t slots = p.path == 0 ? 2048 : kMfmaConcurrentWgs;
+        const int64_t epilogue_steps = p.path == 1 ? 20 : (p.path == 2 ? 3 : 4);
+        const int64_t min_steps = p.path == 2 ? 1 : 4;
+        const int64_t max_splits = std::max<int64_t>(1, std::min<int64_t>(steps_total / min_steps, 4096));
         int64_t best = -1;
         for (int64_t s = 1; s <= max_splits; s++) {
             const int64_t rounds = cdiv(tiles * s, slots);
@@ -281,6 +287,10 @@ hipError_t launch_recon_fwd(const FwdPlan &p, int op_dt, const void *X, const vo
     const float dscale = (float)(2.0 / ((double)M * (double)N));
     if (p.path == 1) {
         hipError_t e = launch_fwd_mfma(X, W, M, N, K, Yref, dY, dscale, colpart, st);
+        if (e != hipSuccess) return e;
+    } else if (p.path == 2) {
+        hipError_t e = launch_fwd_f32((int)p.tile_m, static_cast<const float *>(X), static_cast<const float *>(W), M, N, K,
+                                      static_cast<const float *>(Yref), static_cast<float *>(dY), dscale, colpart, st);
         if (e != hipSuccess) return e;
     } else {
         dim3 grid((unsigned)cdiv(N, 64), (unsigned)cdiv(M, 64));
@@ -324,6 +334,12 @@ hipError_t launch_recon_bwd(const BwdPlan &p, int op_dt, int fmt, int sb, int st
         const int direct = p.splits == 1;
         hipError_t e = launch_bwd_mfma(fmt, w_dt, dY, X, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, alpha, ste_clip,
                                        e8m0_floor, direct ? grad_s : part_s, direct ? grad_c : part_c, direct, flag, st);
+        if (e != hipSuccess || direct) return e;
+    } else if (p.path == 2) {
+        const int direct = p.splits == 1;
+        hipError_t e = launch_bwd_f32(fmt, w_dt, static_cast<const float *>(dY), static_cast<const float *>(X), M, N, K,
+                                      p.chunk, p.splits, W, s_fp, c, sb, alpha, ste_clip, e8m0_floor,
+                                      direct ? grad_s : part_s, direct ? grad_c : part_c, direct, G_out, flag, st);
         if (e != hipSuccess || direct) return e;
     } else {
         dim3 grid((unsigned)cdiv(K, 64), (unsigned)cdiv(N, 64), (unsigned)p.splits);

@@ -26,12 +26,10 @@
 //           values plus the same exchange.
 #include "gemm_common.h"
 
-#include <utility>
-
 namespace focus {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
+
 
 namespace {
 
@@ -40,16 +38,6 @@ constexpr int kThreads = 256;         // four waves
 constexpr int kLdsBytes = 160 * 1024; // LDS of one gfx950 CU
 
 static_assert(kTile == kMfmaTileM && kTile == kMfmaTileN && kTile == kMfmaTileK, "tile geometry");
-
-// Raw buffer resources: a load whose offset is at or past num_records returns zeros and a store
-// there is dropped, so bounds are handled by the hardware range check instead of branches (an
-// offset with bit 31 set is always past it, since num_records is kept below 2^31).
-constexpr int kRsrcWord3 = 0x00020000;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, int64_t bytes) {
-    const int64_t n = bytes < 0 ? 0 : (bytes > 0x7FFFFFFF ? 0x7FFFFFFF : bytes);
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)n, kRsrcWord3);
-}
 
 
 
@@ -66,18 +54,6 @@ constexpr int kFwdStageBytes = 2 * kFwdOpBytes;
 #endif
 constexpr int kFwdStages = FOCUS_FWD_STAGES;
 static_assert(kFwdStages >= 4 && kFwdStages * kFwdStageBytes <= kLdsBytes, "forward stages fit the LDS");
-
-typedef __attribute__((address_space(3))) char lds_char;
-
-// Row `row`'s xor key for the 64-byte-row tile: ((row >> 1) & 3) ^ ((row >> 3) & 1). A fragment
-// read serves 8 or 16 consecutive rows of one logical chunk per cycle; with this key those rows
-// land on distinct 16-byte slots of a 128- or 256-byte bank span.
-__device__ __forceinline__ uint32_t fwd_key(uint32_t row) { return ((row >> 1) & 3u) ^ ((row >> 3) & 1u); }
-
-// Byte offset of 16-byte chunk `chunk` (0..3) of row `row` in a 64-byte-row tile.
-__device__ __forceinline__ uint32_t fwd_off(uint32_t row, uint32_t chunk) {
-    return row * 64u + ((chunk ^ fwd_key(row)) << 4);
-}
 
 // A direct-to-LDS load writes lane L's 16 bytes at LDS byte 16 L from the instruction's base, so
 // each wave fills 1 KB blocks: lane L of block q lands in row 16 q + L / 4, physical chunk L % 4,
@@ -153,9 +129,6 @@ struct BwdDma {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst + (wave * 4 + i) * 1024, 16, (int)off[i], 0, 0, 0);
     }
 };
-
-// s_waitcnt with vmcnt <= n (n < 64) and the LDS and export counters unconstrained
-#define FOCUS_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
 // Fragments of one k16 step: A rows / B columns of the wave's 128 x 128 sub-tile.
 struct Frags {
@@ -254,13 +227,6 @@ __device__ __forceinline__ void tr_wait15(Frags &f) {
                    "+v"(f.b[2]), "+v"(f.b[3]));
 }
 
-// Workgroups are dealt to the 8 XCDs round-robin (id % 8), each XCD with its own L2. Renumbering
-// so that XCD x runs a contiguous block of tiles keeps tiles that share operand panels in one L2.
-__device__ __forceinline__ uint32_t xcd_tile(uint32_t id, uint32_t count) {
-    const uint32_t per = count / 8u;
-    return id < per * 8u ? (id % 8u) * per + id / 8u : id;
-}
-
 // Position t of a rows x cols tile grid in grouped order: groups of `group` row-tiles (default 4)
 // are walked column by column, so the ~32 workgroups an XCD runs at once cover about 4 x 8 tiles and
 // share 4 row panels and 8 column panels instead of 1 and 32.
@@ -273,17 +239,6 @@ __device__ __forceinline__ void grouped_tile(uint32_t t, uint32_t rows, uint32_t
     const uint32_t u = t % per_group;
     r = first + u % in_group;
     c = u / in_group;
-}
-
-// Calls f(std::integral_constant<int, 0>) ... f(<N-1>): every accumulator index is then a
-// compile-time constant, so the accumulators stay in registers.
-template <typename F, int... Is>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, Is...>) {
-    (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-    static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 }  // namespace
@@ -648,13 +603,6 @@ fwd_mfma_kernel(const void *__restrict__ X, const void *__restrict__ W, const ui
     if (n0 + t < N) colpart[(int64_t)tm * N + n0 + t] = red[t] + red[kTile + t];
 }
 
-// the value of lane l ^ X (X = 1 or 2), a DPP move within each four lanes
-template <int X>
-__device__ __forceinline__ float quad_xor(float v) {
-    constexpr int kCtrl = X == 1 ? 0xB1 : 0x4E;  // quad_perm [1, 0, 3, 2] / [2, 3, 0, 1]
-    return __uint_as_float(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), kCtrl, 0xF, 0xF, true));
-}
-
 // Fused straight-through epilogue of the backward kernels on G^T = acc (a 256 k x 256 n tile):
 // per-split partial sums of G m w per sub-block and of G (q - m u) per block or, where the token range
 // is not split (`direct`), the gradients themselves.
@@ -679,7 +627,6 @@ __device__ __forceinline__ void ste_epilogue_n(const f32x16_t (&acc)[4][4], int6
                                                uint32_t *flag, char *smem) {
     constexpr int B = block_of(FMT);
     constexpr int WB = WDT == kBF16 ? 2 : 4;      // bytes per weight element
-    constexpr int EPC = 8 / NCOEF;                // elements per coefficient within a thread's 8
     constexpr int kItems = 8;                     // 8-element pieces per thread and quarter
     constexpr int kWords = WB * 8 / 16;           // 16-byte words of W per piece
     constexpr uint32_t kQuarter = 64u * 1024u;
@@ -688,7 +635,6 @@ __device__ __forceinline__ void ste_epilogue_n(const f32x16_t (&acc)[4][4], int6
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
     const int lr = lane & 31, lh = lane >> 5;
     const float alpha = FMT == kFmtNV ? *alpha_ptr : 1.0f;
-    const float lim = ste_clip ? 6.0f : __builtin_inff();
     const int64_t nb = K / B, ns = K >> sb_log2;
     const bool has_c = c != nullptr;
     bool bad = false;
@@ -787,52 +733,18 @@ __device__ __forceinline__ void ste_epilogue_n(const f32x16_t (&acc)[4][4], int6
             uint32_t byte;
             bool nan = false;
             const float sdq = weight_sdq(FMT, sv[i], alpha, e8m0_floor, byte, nan);
-            float cw[NCOEF], sq[NCOEF];
+            float cw[NCOEF];
 #pragma unroll
             for (int k = 0; k < NCOEF; k++) {
                 cw[k] = has_c ? cv[i][k] : 1.0f;
                 nan = nan || bad_coeff(cw[k]);
-                sq[k] = sdq * cw[k];
-                fast = fast && scale_in_fast_range(sq[k]);
             }
             bad = bad || (ok && nan);
             if (q < 3u) load_item(i, q + 1u);  // the next quarter's piece, into the registers just read
-            float tc[NCOEF], ts = 0.0f;  // sums of G m w per sub-block and of G (q - m u)
-#pragma unroll
-            for (int k = 0; k < NCOEF; k++) tc[k] = 0.0f;
-            if (__builtin_expect(__all(fast || !ok), 1)) {
-                // (a piece outside the tensor may divide by zero here; nothing of it is stored, and the other
-                // pieces of its block lie outside too)
-                float u[8], qv[8];
-#pragma unroll
-                for (int k = 0; k < NCOEF; k++) {
-                    const float y = 1.0f / sq[k];
-#pragma unroll
-                    for (int e = k * EPC; e < (k + 1) * EPC; e++) u[e] = div_by_scale(w[e], sq[k], y);
-                }
-                uint32_t p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, u[0], u[1], 1.0f, 0);
-                p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, u[2], u[3], 1.0f, 1);
-                p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, u[4], u[5], 1.0f, 2);
-                p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, u[6], u[7], 1.0f, 3);
-                e2m1_value2<0>(p, qv[0], qv[1]);
-                e2m1_value2<1>(p, qv[2], qv[3]);
-                e2m1_value2<2>(p, qv[4], qv[5]);
-                e2m1_value2<3>(p, qv[6], qv[7]);
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const bool m = __builtin_fabsf(u[e]) <= lim;
-                    tc[e / EPC] = __builtin_fmaf(g[e], m ? w[e] : 0.0f, tc[e / EPC]);
-                    ts = __builtin_fmaf(g[e], qv[e] - (m ? u[e] : 0.0f), ts);
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    float a1, a2;
-                    ste_terms(g[e], w[e], sdq, cw[e / EPC], ste_clip != 0, a1, a2);
-                    tc[e / EPC] += a1;
-                    ts += a2;
-                }
-            }
+            // (a piece outside the tensor may divide by zero here; nothing of it is stored, and the other
+            // pieces of its block lie outside too)
+            float tc[NCOEF], ts;
+            ste_piece<NCOEF>(g, w, sdq, cw, fast, ok, ste_clip, tc, ts);
             const uint32_t drop = ok ? 0u : 0x80000000u;
             if constexpr (NCOEF == 1) {
                 if (sb_log2 >= 4) tc[0] += quad_xor<1>(tc[0]);

@@ -41,7 +41,8 @@ hipError_t launch_fq_bwd(int fmt, int w_dt, const float *G, int64_t rows, int64_
 // ---- reconstruction GEMMs ----------------------------------------------------------------------
 // Geometry of a forward launch: output tiles of tm x tn; column partial sums [mtiles][N] (double).
 struct FwdPlan {
-    int path;       // 0 = VALU (fp32 / small), 1 = MFMA bf16
+    int path;       // 0 = VALU, 1 = MFMA bf16, 2 = MFMA fp32
+    int64_t tile_m; // rows of an output tile
     int64_t mtiles;
     size_t ws_bytes;
 };
