@@ -298,7 +298,8 @@ focus_status focus_fakequant_weights(const focus_qconfig *q, int w_dtype, int wh
  * fake-quantised weight of the forward. The result is the gradient of the fake-quantised input;
  * focus_fakequant_act_bwd carries it through the activation quantisation. N % 16 == 0 (N == 0
  * writes zeros; dY and W_hat may then be NULL); all pointers 16-byte aligned; ws: focus_workspace_size(FOCUS_CALL_RECON_GEMM_DX, NULL, M, N, K)
- * bytes (it holds the transposed W_hat). bf16 runs on the MFMA path where the shapes allow it. */
+ * bytes (fp32: the transposed W_hat; bf16: the fp32 partial sums where the n range is split over workgroups).
+ * bf16 runs on the MFMA path where the shapes allow it. */
 focus_status focus_recon_gemm_dx(const void *dY, const void *W_hat, int op_dtype, int64_t M, int64_t N, int64_t K,
                                  void *dX_hat, void *ws, size_t ws_bytes, focus_stream stream);
 

@@ -67,10 +67,8 @@ focus_status hip_status(hipError_t e) { return e == hipSuccess ? FOCUS_OK : FOCU
 
 size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
-// dX_hat workspace: header, the transposed W_hat [K][N] (fp32 size, the larger), then the forward's own
 size_t dx_ws(int64_t M, int64_t N, int64_t K) {
-    return kWsHeader + round256((size_t)N * (size_t)K * sizeof(float)) +
-           std::max(plan_fwd(kF32, M, K, N).ws_bytes, plan_fwd(kBF16, M, K, N).ws_bytes);
+    return std::max(plan_dx(kF32, M, N, K).ws_bytes, plan_dx(kBF16, M, N, K).ws_bytes);
 }
 
 size_t fwd_ws(int64_t M, int64_t N, int64_t K) {
@@ -384,18 +382,11 @@ focus_status focus_recon_gemm_dx(const void *dY, const void *W_hat, int op_dtype
     FOCUS_TRY(check_ws(ws, ws_bytes, dx_ws(M, N, K)));
     if (M == 0 || K == 0) return FOCUS_OK;
     const hipStream_t st = (hipStream_t)stream;
-    char *wt = static_cast<char *>(ws) + kWsHeader;
-    char *ws_fwd = wt + round256((size_t)N * (size_t)K * sizeof(float));
     if (N == 0) {  // an empty sum: dX_hat = 0
         const size_t esz = op_dtype == FOCUS_BF16 ? 2 : 4;
         return hip_status(launch_zero_fill(dX_hat, (size_t)M * (size_t)K * esz, st));
     }
-    hipError_t e = launch_transpose(op_dtype, W_hat, N, K, wt, st);
-    if (e != hipSuccess) return hip_status(e);
-    // dX_hat [M][K] = dY [M][N] (W_hat^T [K][N])^T: the forward GEMM's plain product with N as the
-    // contraction
-    const FwdPlan p = plan_fwd(op_dtype, M, K, N);
-    return hip_status(launch_recon_fwd(p, op_dtype, dY, wt, M, K, N, nullptr, dX_hat, nullptr, nullptr, ws_fwd, st));
+    return hip_status(launch_recon_dx(plan_dx(op_dtype, M, N, K), op_dtype, dY, W_hat, M, N, K, dX_hat, ws, st));
 }
 
 focus_status focus_fakequant_act_bwd(const focus_qconfig *q, const void *X, int x_dtype, int64_t rows, int64_t K,

@@ -303,6 +303,45 @@ hipError_t launch_recon_fwd(const FwdPlan &p, int op_dt, const void *X, const vo
     return launch_fwd_finish(p.mtiles, M, N, colpart, col_sq, loss_out, st);
 }
 
+DxPlan plan_dx(int op_dt, int64_t M, int64_t N, int64_t K) {
+    DxPlan p{0, 1, N, 0};
+    if (op_dt != kBF16 || !mfma_dx_supported(M, N, K)) {  // (M and K are positive past this)
+        p.ws_bytes = kWsHeader + ((size_t)N * (size_t)K * sizeof(float) + 255) / 256 * 256 + plan_fwd(op_dt, M, K, N).ws_bytes;
+        return p;
+    }
+    p.path = 1;
+    // Few output tiles leave CUs idle, so the n range is split to fill the chip in whole rounds: minimise
+    // rounds * (32-n steps per split + 8 for the tile's end) plus the traffic of the splits' fp32 sums, written and
+    // read once (about 4 MB in the time of a step), each split keeping >= 8 steps; at most 256 MB of sums, and
+    // none where the tiles already make four rounds.
+    const int64_t tiles = cdiv(M, kMfmaTileM) * cdiv(K, kMfmaTileK), steps = cdiv(std::max<int64_t>(N, 1), 32);
+    int64_t best = -1;
+    const int64_t most = tiles >= 4 * kMfmaConcurrentWgs
+                             ? 1
+                             : std::min<int64_t>(std::min<int64_t>(steps / 8, 64), (int64_t(1) << 26) / (M * K));
+    for (int64_t s = 1; s <= std::max<int64_t>(1, most); s++) {
+        const int64_t cost = cdiv(tiles * s, kMfmaConcurrentWgs) * (cdiv(steps, s) + 8) +
+                             (s > 1 ? s * M * K * 8 / 4000000 + 4 : 0);
+        if (best < 0 || cost < best) best = cost, p.splits = s;
+    }
+    p.chunk = cdiv(steps, p.splits) * 32;
+    p.splits = std::max<int64_t>(1, cdiv(N, p.chunk));
+    p.ws_bytes = kWsHeader + (p.splits > 1 ? (size_t)(p.splits * M * K) * sizeof(float) : 0);
+    return p;
+}
+
+hipError_t launch_recon_dx(const DxPlan &p, int op_dt, const void *dY, const void *W_hat, int64_t M, int64_t N, int64_t K,
+                           void *dX, void *ws, hipStream_t st) {
+    char *const base = static_cast<char *>(ws) + kWsHeader;
+    if (p.path == 1)
+        return launch_dx_mfma(dY, W_hat, M, N, K, p.chunk, p.splits, dX, reinterpret_cast<float *>(base), st);
+    hipError_t e = launch_transpose(op_dt, W_hat, N, K, base, st);
+    if (e != hipSuccess) return e;
+    // dX_hat [M][K] = dY [M][N] (W_hat^T [K][N])^T: the forward GEMM's plain product with N as the contraction
+    return launch_recon_fwd(plan_fwd(op_dt, M, K, N), op_dt, dY, base, M, K, N, nullptr, dX, nullptr, nullptr,
+                            base + ((size_t)N * (size_t)K * sizeof(float) + 255) / 256 * 256, st);
+}
+
 hipError_t launch_fwd_finish(int64_t mtiles, int64_t M, int64_t N, const double *colpart, double *col_sq,
                              double *loss_out, hipStream_t st) {
     colsum_kernel<<<(unsigned)cdiv(N, 16), 256, 0, st>>>(colpart, mtiles, N, col_sq);

@@ -155,6 +155,10 @@ bool mfma_fwd_supported(int64_t M, int64_t N, int64_t K);
 bool mfma_bwd_supported(int64_t M, int64_t N, int64_t K);
 hipError_t launch_fwd_mfma(const void *X, const void *W, int64_t M, int64_t N, int64_t K, const void *Yref,
                            void *dY, float dscale, double *colpart, hipStream_t st);
+// dX_hat = dY W_hat (bf16); with splits > 1 through `splits` x [M][K] fp32 sums in `part`
+bool mfma_dx_supported(int64_t M, int64_t N, int64_t K);
+hipError_t launch_dx_mfma(const void *dY, const void *W, int64_t M, int64_t N, int64_t K, int64_t chunk, int64_t splits,
+                          void *dX, float *part, hipStream_t st);
 // the same product from packed MXFP4 operands (X codes [M][K/2], W codes in K-slabs [K/128][N][64],
 // block-major E8M0 bytes [K/32][rows]; K % 128 == 0)
 bool mfma_fwd_mx_supported(int64_t M, int64_t N, int64_t K);

@@ -6,7 +6,8 @@
 // direct-to-LDS buffer loads (buffer_load ... lds), several steps ahead of the MFMAs:
 //   forward : 32 of K per step (128 for packed MXFP4 operands) in 5 (4) stages;
 //   backward: 32 tokens per step in 4 stages; with packed MXFP4 X_hat, 5 stages of dY, codes and
-//             scale bytes, whose codes are converted to bf16 into 3 further stages.
+//             scale bytes, whose codes are converted to bf16 into 3 further stages;
+//   input gradient: 32 out features per step in 4 stages.
 // The fragments of each half-step (16 of the reduction) are read from LDS one whole step before
 // their MFMAs, into one of three register sets that rotate over a three-step unrolled loop.
 //
@@ -178,6 +179,15 @@ __device__ __forceinline__ i16x4_t ds_read_tr(uint32_t addr) {
     return r;
 }
 
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+
+template <int OFF>
+__device__ __forceinline__ u32x4_t ds_read_b128(uint32_t addr) {
+    u32x4_t r;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF));
+    return r;
+}
+
 // Two fp32 values rounded to bf16 (to nearest, ties to even) in one instruction: lo in bits 0-15,
 // hi in bits 16-31. Written out because the toolchain in use miscompiles the two-element vector
 // conversion for gfx950 (it converts the first element only).
@@ -215,6 +225,13 @@ __device__ __forceinline__ void load_frags_tr(Frags &f, uint32_t base, const uin
 
 __device__ __forceinline__ void tr_wait(Frags &f) {
     asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1]),
+                   "+v"(f.b[2]), "+v"(f.b[3]));
+}
+
+// The same for a set of 12 reads followed by 12 others
+__device__ __forceinline__ void tr_wait12(Frags &f) {
+    asm volatile("s_waitcnt lgkmcnt(12)"
                  : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1]),
                    "+v"(f.b[2]), "+v"(f.b[3]));
 }
@@ -908,15 +925,6 @@ constexpr int kMxLdsBytes = kMxAOff + kMxAStages * kBwdOpBytes;
 constexpr int kMxLoads = 6;  // loads per slot per thread: dY 4, codes 1, scales 1
 static_assert(kMxLdsBytes <= kLdsBytes, "MXFP4 backward stages fit the LDS");
 
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-
-template <int OFF>
-__device__ __forceinline__ u32x4_t ds_read_b128(uint32_t addr) {
-    u32x4_t r;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF));
-    return r;
-}
-
 template <int OFF>
 __device__ __forceinline__ uint32_t ds_read_u8(uint32_t addr) {
     uint32_t r;
@@ -1169,6 +1177,177 @@ bwd_mfma_mx_kernel(const uint16_t *__restrict__ dY, const uint8_t *__restrict__ 
                               part_c, direct, flag, smem);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Input gradient dX_hat = dY W_hat: rows = tokens, columns = in features k, the reduction over the out
+// features n. dY [M][N] is contiguous along the reduction and staged and read as the forward's operands;
+// W_hat [N][K] is reduction-major and staged and read (transposing) as the backward's, so no transposed copy of
+// it is made. Pipeline and fragment sets of the backward, 32 n per step. With splits > 1 each workgroup covers
+// `chunk` of the n range and writes fp32 sums to part [split][M][K], which dx_finish_kernel adds up.
+// Against a transposed copy of W_hat and the forward kernel, one 256 x 256 tile per workgroup whatever their
+// number: 4,096 x 32,000 x 2,560 (160 tiles, 3 splits) 587 us for 895, 640 x 31,808 x 1,184 65 for 590,
+// 65,536 x 9,728 x 2,560 (no splits) 2.63 ms for 2.71.
+__global__ void __launch_bounds__(kThreads, 1)
+dx_mfma_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ W, int64_t M, int64_t N, int64_t K,
+               int64_t chunk, uint16_t *__restrict__ dX, float *__restrict__ part, int tiles_k) {
+    constexpr int S = kBwdStages;
+    __shared__ __attribute__((aligned(16))) char smem[S * kBwdStageBytes];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    const int lr = lane & 31, lh = lane >> 5;
+    // splits outermost, as in the backward
+    const uint32_t id = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+    uint32_t tm, tk;
+    grouped_tile(id % gridDim.x, gridDim.x / tiles_k, tiles_k, tm, tk);
+    const int64_t m0 = (int64_t)tm * kTile, k0 = (int64_t)tk * kTile;
+    const int64_t split = id / gridDim.x;
+    const int64_t n_begin = split * chunk, n_end = std::min<int64_t>(N, n_begin + chunk);
+
+    f32x16_t acc[4][4];
+    const f32x16_t zero = {};
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc[i][j] = zero;
+
+    lds_char *const lsm = (lds_char *)smem;
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int64_t pitch = N * 2;
+    FwdDma pa;
+    pa.init(pitch, wave_u, lane);
+    BwdDma pb;
+    pb.init(K, k0, wave_u, lane);
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(dY + m0 * N, (M - m0) * pitch);
+    const int64_t nk = n_end > n_begin ? (n_end - n_begin + kBwdStep - 1) / kBwdStep : 0;
+    // offset bits of step j's dY loads: bytes past the row's end and steps past the range read as zeros
+    auto a_bad = [&](int64_t j) { return j < nk ? pa.step_bad(pitch, n_begin * 2 + j * 64) : 0x80000000u; };
+    auto a_base = [&](int64_t j) { return (uint32_t)(n_begin * 2 + j * 64); };
+#pragma unroll
+    for (int s0 = 0; s0 < S - 1; s0++) {
+        const __amdgpu_buffer_rsrc_t rb = BwdDma::step_rsrc(W, K, n_begin + s0 * kBwdStep, n_end);
+        lds_char *st = lsm + s0 * kBwdStageBytes;
+#pragma unroll
+        for (int i = 0; i < 4; i++) pa.issue_one(ra, a_base(s0), a_bad(s0), st, wave_u, i);
+#pragma unroll
+        for (int i = 0; i < 4; i++) pb.issue_one(rb, st + kBwdOpBytes, wave_u, i);
+    }
+    uint32_t a_off[2], b_off[4];
+#pragma unroll
+    for (int ks = 0; ks < 2; ks++) a_off[ks] = fwd_off(wm * 128 + lr, ks * 2 + lh);  // row + 32: 2 KB further
+#pragma unroll
+    for (int i = 0; i < 4; i++) b_off[i] = tr_lane_off(wn * 128 + i * 32, lane);
+    // the 12 reads of a k16 step's fragments
+    auto frags = [&](auto ks, Frags &f, uint32_t base) {
+        constexpr int kRow = decltype(ks)::value * 16 * kBwdRowBytes;
+        static_for<4>([&](auto i) {
+            f.a[i] = __builtin_bit_cast(bf16x8_t, ds_read_b128<2048 * decltype(i)::value>(base + a_off[ks]));
+            const i16x4_t b_lo = ds_read_tr<kBwdOpBytes + kRow>(base + b_off[i]);
+            const i16x4_t b_hi = ds_read_tr<kBwdOpBytes + kRow + 4 * kBwdRowBytes>(base + b_off[i]);
+            const i16x4_t vb[2] = {b_lo, b_hi};
+            f.b[i] = __builtin_bit_cast(bf16x8_t, vb);
+        });
+    };
+    constexpr std::integral_constant<int, 0> k_lo{};
+    constexpr std::integral_constant<int, 1> k_hi{};
+    const uint32_t lds0 = lds_addr(smem);
+    FOCUS_WAIT_VMCNT(16);
+    asm volatile("s_barrier" ::: "memory");
+    Frags f, g, h;
+    frags(k_lo, f, lds0);
+    frags(k_hi, g, lds0);
+    auto step = [&](int64_t kt, Frags &P, Frags &Q, Frags &R) {
+        const uint32_t nxt = lds0 + (uint32_t)((kt + 1) & 3) * kBwdStageBytes;
+        const __amdgpu_buffer_rsrc_t rb = BwdDma::step_rsrc(W, K, n_begin + (kt + 3) * kBwdStep, n_end);
+        const uint32_t base = a_base(kt + 3), bad = a_bad(kt + 3);
+        lds_char *st = lsm + (int)((kt + 3) & 3) * kBwdStageBytes;
+        // slot kt + 1 and this thread's reads of P have landed (only the 12 of Q may be in flight); after the
+        // barrier everyone's have, and stage (kt - 1) % 4 is free for slot kt + 3
+        FOCUS_WAIT_VMCNT(8);
+        tr_wait12(P);
+        asm volatile("s_barrier" ::: "memory");
+        frags(k_lo, R, nxt);
+        static_for<16>([&](auto idx) {
+            constexpr int i = idx / 4, jj = idx % 4;
+            acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(P.a[i], P.b[jj], acc[i][jj], 0, 0, 0);
+            if constexpr (idx % 2 == 1) {
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (idx / 2 < 4) pa.issue_one(ra, base, bad, st, wave_u, idx / 2);
+                else pb.issue_one(rb, st + kBwdOpBytes, wave_u, idx / 2 - 4);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
+        tr_wait12(Q);  // read during step kt - 1
+        frags(k_hi, P, nxt);
+        mma_frags(Q, acc);
+    };
+    int64_t kt = 0;
+    for (; kt + 3 <= nk; kt += 3) {
+        step(kt, f, g, h);
+        step(kt + 1, h, f, g);
+        step(kt + 2, g, h, f);
+    }
+    if (kt < nk) step(kt, f, g, h);
+    if (kt + 1 < nk) step(kt + 1, h, f, g);
+    // no read may still be in flight when the registers and the LDS are used again, and no empty slot's zeros
+    tr_wait(f), tr_wait(g), tr_wait(h);
+    FOCUS_WAIT_VMCNT(0);
+    // acc[i][j][r] is element (m, k) = (m0 + 128 wm + 32 i + 8 (r / 4) + 4 lh + r % 4, k0 + 128 wn + 32 j + lr)
+    if (part) {
+        const uint32_t K32 = (uint32_t)K;
+        const __amdgpu_buffer_rsrc_t rp = make_rsrc(part + (split * M + m0) * K, (M - m0) * K * 4);
+        static_for<4>([&](auto j) {
+            const uint32_t k = (uint32_t)k0 + wn * 128 + j * 32 + lr, past = (uint32_t)(k >= K32) << 31;
+            static_for<4>([&](auto i) {
+                static_for<16>([&](auto r) {
+                    const uint32_t m = wm * 128 + i * 32 + 8 * (r / 4) + 4 * lh + r % 4;
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][(int)r]), rp,
+                                                          (int)(((m * K32 + k) * 4u) | past), 0, 0);
+                });
+            });
+        });
+        return;
+    }
+    // bf16 through LDS, 64 rows x 256 columns at a time (accumulator row block i of every wave), two buffers:
+    // one barrier per quarter, 16-byte stores. The xor on the 16-byte chunk index spreads the rows over banks.
+    const __amdgpu_buffer_rsrc_t rd = make_rsrc(dX + m0 * K, (M - m0) * K * 2);
+    auto q_off = [](uint32_t rl, uint32_t ch) { return rl * 512u + ((ch ^ (((rl & 3u) << 1) ^ (((rl >> 2) & 1u) << 2))) << 4); };
+    __syncthreads();  // every wave is done with the operand stages
+    static_for<4>([&](auto q) {
+        char *const buf = smem + (q & 1) * 32768;
+        static_for<4>([&](auto j) {
+            const uint32_t col = wn * 128 + j * 32 + lr;
+            static_for<8>([&](auto h2) {
+                constexpr int r = 2 * h2;
+                const uint32_t pk = cvt_pk_bf16(acc[q][j][r], acc[q][j][r + 1]);
+                const uint32_t rl = wm * 32 + 8 * (r / 4) + 4 * lh + r % 4;
+                *reinterpret_cast<uint16_t *>(buf + q_off(rl, col >> 3) + (col & 7u) * 2u) = (uint16_t)pk;
+                *reinterpret_cast<uint16_t *>(buf + q_off(rl + 1, col >> 3) + (col & 7u) * 2u) = (uint16_t)(pk >> 16);
+            });
+        });
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const uint32_t rl = ((uint32_t)t >> 5) + 8u * i, ch = (uint32_t)t & 31u;
+            const uint32_t row = (rl >> 5) * 128u + (uint32_t)q * 32u + (rl & 31u), k = (uint32_t)k0 + ch * 8u;
+            const u32x4_t v = *reinterpret_cast<const u32x4_t *>(buf + q_off(rl, ch));
+            __builtin_amdgcn_raw_buffer_store_b128(v, rd, (int)(((row * (uint32_t)K + k) * 2u) | (uint32_t)(k >= (uint32_t)K) << 31), 0, 0);
+        }
+    });
+}
+
+// dX_hat = the splits' sums added in order, rounded to bf16 once; 8 elements per thread
+__global__ void __launch_bounds__(256)
+dx_finish_kernel(const float *__restrict__ part, int64_t splits, int64_t n, uint16_t *__restrict__ dX) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+    if (i >= n) return;
+    float s[8], v[8];
+    load8(part, kF32, i, s);
+    for (int64_t z = 1; z < splits; z++) {
+        load8(part, kF32, z * n + i, v);
+#pragma unroll
+        for (int e = 0; e < 8; e++) s[e] += v[e];
+    }
+    store8(dX, kBF16, i, s);
+}
+
 // ================================================================================================
 
 // Buffer offsets are 32-bit: a tile's rows must span less than 2^31 bytes.
@@ -1191,6 +1370,23 @@ hipError_t launch_fwd_mfma(const void *X, const void *W, int64_t M, int64_t N, i
     uint16_t *d = static_cast<uint16_t *>(dY);
     if (Yref) fwd_mfma_kernel<true, false><<<grid, kThreads, 0, st>>>(X, W, nullptr, nullptr, M, N, K, y, d, dscale, colpart, tiles_n);
     else fwd_mfma_kernel<false, false><<<grid, kThreads, 0, st>>>(X, W, nullptr, nullptr, M, N, K, y, d, dscale, colpart, tiles_n);
+    return hipGetLastError();
+}
+
+bool mfma_dx_supported(int64_t M, int64_t N, int64_t K) {
+    return M > 0 && K > 0 && K % 8 == 0 && N % 16 == 0 && int64_t(kTile) * N * 2 < (int64_t(1) << 31) &&
+           int64_t(kTile) * K * 4 < (int64_t(1) << 31) && int64_t(kBwdStep) * K * 2 < (int64_t(1) << 31) &&
+           (M + kTile - 1) / kTile * ((K + kTile - 1) / kTile) < (int64_t(1) << 31);
+}
+
+hipError_t launch_dx_mfma(const void *dY, const void *W, int64_t M, int64_t N, int64_t K, int64_t chunk, int64_t splits,
+                          void *dX, float *part, hipStream_t st) {
+    const int tiles_m = (int)((M + kTile - 1) / kTile), tiles_k = (int)((K + kTile - 1) / kTile);
+    const dim3 grid((unsigned)tiles_m * tiles_k, (unsigned)splits);
+    uint16_t *d = static_cast<uint16_t *>(dX);
+    dx_mfma_kernel<<<grid, kThreads, 0, st>>>(static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(W), M, N, K,
+                                              chunk, d, splits > 1 ? part : nullptr, tiles_k);
+    if (splits > 1) dx_finish_kernel<<<(unsigned)((M * K / 8 + 255) / 256), 256, 0, st>>>(part, splits, M * K, d);
     return hipGetLastError();
 }
 

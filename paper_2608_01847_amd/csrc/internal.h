@@ -55,6 +55,18 @@ struct BwdPlan {
     size_t ws_bytes;
 };
 
+// Geometry of an input-gradient launch: fp32 goes through a transposed W_hat and the forward (path 0), bf16
+// reads W_hat as it lies (path 1), the n range split `splits` ways with `chunk` of n per split.
+struct DxPlan {
+    int path;
+    int64_t splits;
+    int64_t chunk;
+    size_t ws_bytes;
+};
+
+DxPlan plan_dx(int op_dt, int64_t M, int64_t N, int64_t K);
+hipError_t launch_recon_dx(const DxPlan &p, int op_dt, const void *dY, const void *W_hat, int64_t M, int64_t N, int64_t K,
+                           void *dX, void *ws, hipStream_t st);
 FwdPlan plan_fwd(int op_dt, int64_t M, int64_t N, int64_t K);
 BwdPlan plan_bwd(int op_dt, int fmt, int sb, int64_t M, int64_t N, int64_t K, bool want_G);
 

@@ -167,3 +167,16 @@ def test_kl_top_stack_training_lowers_the_loss(F, fmt):
         r = calib.kl_top_epoch(fmt, v)
         assert r["eval_after"] < 0.95 * r["eval_before"], (v, r["eval_before"], r["eval_after"])
         assert r["train_curve"][-1] < r["train_curve"][0], (v, r["train_curve"][0], r["train_curve"][-1])
+
+
+# tile and step edges of the bf16 input gradient, one n range and several (the last may be ragged), against
+# integers: the products and sums are integers below 2^24, so dX_hat is the exact sum rounded to bf16 once
+@pytest.mark.parametrize("M,N,K", [(1, 16, 8), (255, 32, 264), (256, 48, 256), (257, 304, 520), (300, 4112, 256),
+                                   (64, 8000, 1032), (513, 1040, 16)])
+def test_recon_gemm_dx_is_exact_on_integers(F, M, N, K):
+    announce(f"dx exact M={M} N={N} K={K}")
+    g = torch.Generator().manual_seed(M + N + K)
+    dY = torch.randint(-3, 4, (M, N), generator=g).to(torch.bfloat16)
+    W = torch.randint(-3, 4, (N, K), generator=g).to(torch.bfloat16)
+    dX = F.recon_gemm_dx(dY.cuda(), W.cuda())
+    assert torch.equal(dX.cpu(), (dY.double() @ W.double()).float().to(torch.bfloat16))
