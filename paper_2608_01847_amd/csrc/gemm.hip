@@ -202,6 +202,49 @@ loss_kernel(const double *__restrict__ col_sq, int64_t N, double inv_mn, double 
     if (threadIdx.x == 0) *loss = red[0] * inv_mn;
 }
 
+// Both of the above in one workgroup, where the partials are few (a launch costs more than their sums): a thread per
+// column, the same order of additions. 4 x 256 partials take 3.9 us,
+// where the two kernels take 4.4 and a launch more; at 16 x 1,024 (7.7) it is no longer ahead.
+constexpr int kFinishCols = 1024;
+constexpr int64_t kFinishParts = 4096;
+__global__ void __launch_bounds__(1024)
+fwd_finish_small_kernel(const double *__restrict__ colpart, int64_t mtiles, int64_t N, double *__restrict__ col_sq,
+                        double inv_mn, double *__restrict__ loss) {
+    __shared__ double cols[kFinishCols];
+    __shared__ double part[256];
+    for (int64_t n = threadIdx.x; n < N; n += 1024) {
+        double s[16];
+#pragma unroll
+        for (int g = 0; g < 16; g++) s[g] = 0.0;
+        for (int64_t m0 = 0; m0 < mtiles; m0 += 16) {
+#pragma unroll
+            for (int g = 0; g < 16; g++) {
+                const int64_t mt = std::min<int64_t>(m0 + g, mtiles - 1);  // in bounds, left out past the last
+                const double v = colpart[mt * N + n];
+                s[g] += m0 + g < mtiles ? v : 0.0;
+            }
+        }
+#pragma unroll
+        for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+            for (int g = 0; g < w; g++) s[g] += s[g + w];
+        col_sq[n] = cols[n] = s[0];
+    }
+    __syncthreads();
+    if (!loss) return;
+    double s = 0.0;
+    if (threadIdx.x < 256) {
+        for (int64_t n = threadIdx.x; n < N; n += 256) s += cols[n];
+        part[threadIdx.x] = s;
+    }
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *loss = part[0] * inv_mn;
+}
+
 // grad_c = -(sum over splits of part_c) / c^2 ; grad_s = f * (sum over splits of part_s)
 __global__ void __launch_bounds__(256)
 bwd_finish_kernel(const float *__restrict__ part_s, const float *__restrict__ part_c, int64_t splits,
@@ -229,13 +272,21 @@ bwd_finish_kernel(const float *__restrict__ part_s, const float *__restrict__ pa
 
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Rows of a bf16 / MXFP4 forward tile: 128 x 128 tiles while they are at most two (MXFP4) or one and a half (bf16)
+// per CU, else 256 x 256. With 264 small tiles (3,000 x 1,368 x 2,176) they took 22.3 and 40.6 us for 32.5 and 55.9,
+// with 512 (2,048 x 4,096 x 4,096) 36.8 and 109 for 43.6 and 99, with 960 40 and 85 for 33 and 61.
+static int64_t fwd_tile_rows(int64_t M, int64_t N, bool mx) {
+    return cdiv(M, kSmallTile) * cdiv(N, kSmallTile) <= (mx ? 2 * kMfmaConcurrentWgs : 3 * kMfmaConcurrentWgs / 2)
+               ? kSmallTile : kMfmaTileM;
+}
+
 FwdPlan plan_fwd(int op_dt, int64_t M, int64_t N, int64_t K) {
     FwdPlan p;
     p.path = op_dt == kBF16 ? (mfma_fwd_supported(M, N, K) ? 1 : 0) : (f32_fwd_supported(M, N, K) ? 2 : 0);
     // fp32: 64 x 64 tiles where they give every CU one, else 32 x 32 with K split over the waves (128 x 256 x
     // 256 has 8 of the former and 32 of the latter)
     const bool small = p.path == 2 && cdiv(M, kF32Tile) * cdiv(N, kF32Tile) < kMfmaConcurrentWgs;
-    p.tile_m = p.path == 1 ? kMfmaTileM : (small ? kF32Tile / 2 : 64);
+    p.tile_m = p.path == 1 ? fwd_tile_rows(M, N, false) : (small ? kF32Tile / 2 : 64);
     p.mtiles = cdiv(M, p.tile_m);
     p.ws_bytes = kWsHeader + (size_t)(p.mtiles * N + N) * sizeof(double);
     return p;
@@ -286,7 +337,9 @@ hipError_t launch_recon_fwd(const FwdPlan &p, int op_dt, const void *X, const vo
     double *col_sq = col_sq_opt ? col_sq_opt : colpart + p.mtiles * N;
     const float dscale = (float)(2.0 / ((double)M * (double)N));
     if (p.path == 1) {
-        hipError_t e = launch_fwd_mfma(X, W, M, N, K, Yref, dY, dscale, colpart, st);
+        hipError_t e = p.tile_m == kSmallTile
+                           ? launch_fwd_small(X, W, nullptr, nullptr, M, N, K, Yref, dY, dscale, colpart, st)
+                           : launch_fwd_mfma(X, W, M, N, K, Yref, dY, dscale, colpart, st);
         if (e != hipSuccess) return e;
     } else if (p.path == 2) {
         hipError_t e = launch_fwd_f32((int)p.tile_m, static_cast<const float *>(X), static_cast<const float *>(W), M, N, K,
@@ -344,6 +397,10 @@ hipError_t launch_recon_dx(const DxPlan &p, int op_dt, const void *dY, const voi
 
 hipError_t launch_fwd_finish(int64_t mtiles, int64_t M, int64_t N, const double *colpart, double *col_sq,
                              double *loss_out, hipStream_t st) {
+    if (N <= kFinishCols && mtiles * N <= kFinishParts) {
+        fwd_finish_small_kernel<<<1, 1024, 0, st>>>(colpart, mtiles, N, col_sq, 1.0 / ((double)M * (double)N), loss_out);
+        return hipGetLastError();
+    }
     colsum_kernel<<<(unsigned)cdiv(N, 16), 256, 0, st>>>(colpart, mtiles, N, col_sq);
     if (loss_out) loss_kernel<<<1, 256, 0, st>>>(col_sq, N, 1.0 / ((double)M * (double)N), loss_out);
     return hipGetLastError();
@@ -352,11 +409,12 @@ hipError_t launch_fwd_finish(int64_t mtiles, int64_t M, int64_t N, const double 
 hipError_t launch_recon_fwd_mx(const void *Xc, const void *Xs, const void *Wc, const void *Ws, int64_t M, int64_t N,
                                int64_t K, const void *Yref, void *dY, double *loss_out, double *col_sq_opt, void *ws,
                                hipStream_t st) {
-    const int64_t mtiles = cdiv(M, kMfmaTileM);
+    const int64_t rows = fwd_tile_rows(M, N, true), mtiles = cdiv(M, rows);
     double *colpart = reinterpret_cast<double *>(reinterpret_cast<char *>(ws) + kWsHeader);
     double *col_sq = col_sq_opt ? col_sq_opt : colpart + mtiles * N;
     const float dscale = (float)(2.0 / ((double)M * (double)N));
-    hipError_t e = launch_fwd_mfma_mx(Xc, Xs, Wc, Ws, M, N, K, Yref, dY, dscale, colpart, st);
+    hipError_t e = rows == kSmallTile ? launch_fwd_small(Xc, Wc, Xs, Ws, M, N, K, Yref, dY, dscale, colpart, st)
+                                      : launch_fwd_mfma_mx(Xc, Xs, Wc, Ws, M, N, K, Yref, dY, dscale, colpart, st);
     if (e != hipSuccess || !Yref) return e;
     return launch_fwd_finish(mtiles, M, N, colpart, col_sq, loss_out, st);
 }

@@ -151,10 +151,15 @@ constexpr int kMfmaTileK = 256;       // backward output tile: in features
 constexpr int kMfmaTokenStep = 64;    // backward reduction step over tokens
 constexpr int kMfmaConcurrentWgs = 256;  // one 128 KB-LDS workgroup per CU, 256 CUs
 
+constexpr int kSmallTile = 128;       // both tile edges of the small-tile kernels (gemm_small.hip)
+
 bool mfma_fwd_supported(int64_t M, int64_t N, int64_t K);
 bool mfma_bwd_supported(int64_t M, int64_t N, int64_t K);
 hipError_t launch_fwd_mfma(const void *X, const void *W, int64_t M, int64_t N, int64_t K, const void *Yref,
                            void *dY, float dscale, double *colpart, hipStream_t st);
+// the forward on 128 x 128 tiles: bf16 operands (Xs == nullptr) or packed MXFP4
+hipError_t launch_fwd_small(const void *X, const void *W, const void *Xs, const void *Ws, int64_t M, int64_t N, int64_t K,
+                            const void *Yref, void *dY, float dscale, double *colpart, hipStream_t st);
 // dX_hat = dY W_hat (bf16); with splits > 1 through `splits` x [M][K] fp32 sums in `part`
 bool mfma_dx_supported(int64_t M, int64_t N, int64_t K);
 hipError_t launch_dx_mfma(const void *dY, const void *W, int64_t M, int64_t N, int64_t K, int64_t chunk, int64_t splits,

@@ -25,11 +25,9 @@
 //           lane holds 4 consecutive k of one n per register group, so a sub-block of 8 is an
 //           in-lane sum of 4 plus one exchange with lane l ^ 32, and a block of 32 is 16 in-lane
 //           values plus the same exchange.
-#include "gemm_common.h"
+#include "mfma_common.h"
 
 namespace focus {
-
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 
 namespace {
@@ -55,37 +53,6 @@ constexpr int kFwdStageBytes = 2 * kFwdOpBytes;
 #endif
 constexpr int kFwdStages = FOCUS_FWD_STAGES;
 static_assert(kFwdStages >= 4 && kFwdStages * kFwdStageBytes <= kLdsBytes, "forward stages fit the LDS");
-
-// A direct-to-LDS load writes lane L's 16 bytes at LDS byte 16 L from the instruction's base, so
-// each wave fills 1 KB blocks: lane L of block q lands in row 16 q + L / 4, physical chunk L % 4,
-// which must hold logical chunk (L % 4) ^ fwd_key(row). The key depends on row bits 1-3 only,
-// i.e. on L alone, so one step offset serves all four blocks. Offsets are in bytes of a row of
-// `pitch` bytes (2 K for bf16 operands, K / 2 for packed FP4 codes); each thread's offsets at the
-// first step are fixed for the whole tile.
-struct FwdDma {
-    uint32_t lane_off[4];
-    uint32_t cb;  // byte offset of this lane's chunk inside a step's 64 bytes of a row
-    __device__ __forceinline__ void init(int64_t pitch, int wave, int lane) {
-        cb = ((uint32_t)(lane & 3) ^ fwd_key((uint32_t)lane >> 2)) * 16u;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const uint32_t row = (wave * 4 + i) * 16 + (lane >> 2);
-            lane_off[i] = row * (uint32_t)pitch + cb;
-        }
-    }
-    // Offset bits of the step whose row bytes start at b0: chunks at or past the row end get bit
-    // 31 set, so they are out of range and read as zeros (an arithmetic mask, not a branch).
-    __device__ __forceinline__ uint32_t step_bad(int64_t pitch, int64_t b0) const {
-        const int32_t lim = (int32_t)(pitch - b0);
-        return ((uint32_t)(lim - 1 - (int32_t)cb) >> 31) << 31;
-    }
-    // Load i (0..3) of this wave for the step whose row bytes start at b0 = base.
-    __device__ __forceinline__ void issue_one(__amdgpu_buffer_rsrc_t rs, uint32_t base, uint32_t bad,
-                                              lds_char *dst, int wave, int i) const {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst + (wave * 4 + i) * 1024, 16,
-                                                 (int)((lane_off[i] + base) | bad), 0, 0, 0);
-    }
-};
 
 // Backward operands are token-major tiles, [32 tokens][256 columns] of bf16, staged as they lie
 // in memory and transposed by the fragment reads. The 16-byte chunk index of a row is xor-ed with
@@ -152,49 +119,6 @@ __device__ __forceinline__ void mma_frags(const Frags &f, f32x16_t (&acc)[4][4])
 #pragma unroll
         for (int j = 0; j < 4; j++)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
-}
-
-// Fragment of 32 operand rows (columns c .. c + 31 of a token-major tile) for the k16 step whose
-// first token row is t0: lane l needs tokens t0 + 8 (l / 32) + 0..7 of column c + l % 32. A
-// transposing read hands lane i of a 16-lane group element i % 4 of the 8-byte pieces addressed
-// by lanes 4 e + i / 4 (e = 0..3); pointing lane j at row t0' + j / 4, columns c' + 4 (j % 4) .. + 3
-// gives lane i tokens t0' .. t0' + 3 of column c' + i. Two reads (rows r and r + 4, the same
-// swizzle) cover the 8 tokens.
-//
-// The reads are issued as inline assembly: the compiler's builtin for them carries no aliasing
-// information, so the compiler would make every such read wait for all direct-to-LDS loads in
-// flight (vmcnt(0)), draining the pipeline each step. The price is that the compiler does not
-// track these reads: `tr_wait` must run before their registers are used, and it takes the
-// fragments as operands so that no consumer can be scheduled above it.
-typedef short i16x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32_t lds_addr(const char *p) {
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
-}
-
-template <int OFF>
-__device__ __forceinline__ i16x4_t ds_read_tr(uint32_t addr) {
-    i16x4_t r;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF));
-    return r;
-}
-
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-
-template <int OFF>
-__device__ __forceinline__ u32x4_t ds_read_b128(uint32_t addr) {
-    u32x4_t r;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "i"(OFF));
-    return r;
-}
-
-// Two fp32 values rounded to bf16 (to nearest, ties to even) in one instruction: lo in bits 0-15,
-// hi in bits 16-31. Written out because the toolchain in use miscompiles the two-element vector
-// conversion for gfx950 (it converts the first element only).
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
-    uint32_t r;
-    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(lo), "v"(hi));
-    return r;
 }
 
 // Per-lane byte offset, inside a tile, of the lower read of the fragment at columns c (step 0).
@@ -307,11 +231,11 @@ fwd_mfma_kernel(const void *__restrict__ X, const void *__restrict__ W, const ui
     const uint32_t sc_row = ((uint32_t)lane >> 5) * 128u + ((uint32_t)lane & 3u) * 32u + (((uint32_t)lane >> 2) & 7u) * 4u;
     const uint32_t sc_b = (uint32_t)lr & 3u;
     const uint32_t sc_sel = sc_b | 0x0C00u | ((4u + sc_b) << 16) | 0x0C000000u;
-    FwdDma dma;  // X and W rows have the same length, so one set of offsets serves both (bf16; X codes)
+    FwdDma<> dma;  // X and W rows have the same length, so one set of offsets serves both (bf16; X codes)
     dma.init(pitch, wave_u, lane);
     // MX: step j's W tile is rows n0 .. n0 + 255 of K-slab j, 64 bytes each, one contiguous run; rows
     // past N are outside the resource and read as zeros
-    FwdDma dmaw;
+    FwdDma<> dmaw;
     dmaw.init(64, wave_u, lane);
     const char *const ws_base = static_cast<const char *>(W) + n0 * 64;
     const int64_t w_slab = N * 64;
@@ -1211,7 +1135,7 @@ dx_mfma_kernel(const uint16_t *__restrict__ dY, const uint16_t *__restrict__ W, 
     lds_char *const lsm = (lds_char *)smem;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const int64_t pitch = N * 2;
-    FwdDma pa;
+    FwdDma<> pa;
     pa.init(pitch, wave_u, lane);
     BwdDma pb;
     pb.init(K, k0, wave_u, lane);
