@@ -295,7 +295,8 @@ FwdPlan plan_fwd(int op_dt, int64_t M, int64_t N, int64_t K) {
 BwdPlan plan_bwd(int op_dt, int fmt, int sb, int64_t M, int64_t N, int64_t K, bool want_G) {
     BwdPlan p;
     p.path = op_dt == kBF16 ? (!want_G && mfma_bwd_supported(M, N, K) ? 1 : 0) : (f32_bwd_supported(M, N, K) ? 2 : 0);
-    const int64_t tn = p.path == 1 ? kMfmaTileN : 64, tk = p.path == 1 ? kMfmaTileK : 64;
+    p.tile = p.path == 1 ? kMfmaTileN : 64;
+    const int64_t tn = p.tile, tk = p.tile;
     const int64_t step = p.path == 1 ? kMfmaTokenStep : (p.path == 2 ? kF32TokenStep : 16);
     const int64_t tiles = cdiv(N, tn) * cdiv(K, tk);
     const int64_t steps_total = cdiv(std::max<int64_t>(M, 1), step);
@@ -320,6 +321,23 @@ BwdPlan plan_bwd(int op_dt, int fmt, int sb, int64_t M, int64_t N, int64_t K, bo
             if (best < 0 || cost < best) {
                 best = cost;
                 splits = s;
+            }
+        }
+        // MFMA path: 128 x 128 tiles, two workgroups per CU, where the large tiles' epilogue would cost more than they
+        // save. Measured, in units of 0.02 us: a 64-token step takes 73 on a large tile (20 of them the epilogue); on
+        // small ones 45 with one workgroup on the CU and 30 for each of two, the epilogue 400 and 325. (2,048 x
+        // 1,024 x 2,560: 26 to 30 us for 39; 3,001 x 1,368 x 2,128: 39 for 47; 5,076 x 3,000 x 1,664: 79 to 95 for 71.)
+        if (p.path == 1) {
+            const int64_t small_tiles = cdiv(N, kSmallTile) * cdiv(K, kSmallTile);
+            int64_t best_small = best * 73;
+            for (int64_t s = 1; s <= std::max<int64_t>(1, steps_total / 2) && small_tiles * s <= 8 * slots; s++) {
+                const int64_t per_cu = cdiv(small_tiles * s, slots), steps = cdiv(steps_total, s);
+                const int64_t cost = per_cu / 2 * 2 * (30 * steps + 325) + per_cu % 2 * (45 * steps + 400);
+                if (cost < best_small) {
+                    best_small = cost;
+                    splits = s;
+                    p.tile = kSmallTile;
+                }
             }
         }
     }
@@ -429,8 +447,12 @@ hipError_t launch_recon_bwd(const BwdPlan &p, int op_dt, int fmt, int sb, int st
     if (p.path == 1) {
         // one split: the kernel writes the gradients, nothing is left to sum
         const int direct = p.splits == 1;
-        hipError_t e = launch_bwd_mfma(fmt, w_dt, dY, X, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, alpha, ste_clip,
-                                       e8m0_floor, direct ? grad_s : part_s, direct ? grad_c : part_c, direct, flag, st);
+        float *const gs = direct ? grad_s : part_s, *const gc = direct ? grad_c : part_c;
+        hipError_t e = p.tile == kSmallTile
+                           ? launch_bwd_small(fmt, w_dt, dY, X, nullptr, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, alpha,
+                                              ste_clip, e8m0_floor, gs, gc, direct, flag, st)
+                           : launch_bwd_mfma(fmt, w_dt, dY, X, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, alpha, ste_clip,
+                                             e8m0_floor, gs, gc, direct, flag, st);
         if (e != hipSuccess || direct) return e;
     } else if (p.path == 2) {
         const int direct = p.splits == 1;
@@ -466,8 +488,12 @@ hipError_t launch_recon_bwd_mx(const BwdPlan &p, int sb, int ste_clip, int e8m0_
     float *part_s = reinterpret_cast<float *>(reinterpret_cast<char *>(ws) + kWsHeader);
     float *part_c = part_s + p.splits * N * nb;
     const int direct = p.splits == 1;  // the kernel writes the gradients, nothing is left to sum
-    hipError_t e = launch_bwd_mfma_mx(w_dt, dY, Xc, Xs, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, ste_clip, e8m0_floor,
-                                      direct ? grad_s : part_s, direct ? grad_c : part_c, direct, flag, st);
+    float *const gs = direct ? grad_s : part_s, *const gc = direct ? grad_c : part_c;
+    hipError_t e = p.tile == kSmallTile
+                       ? launch_bwd_small(kFmtMX, w_dt, dY, Xc, Xs, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, nullptr,
+                                          ste_clip, e8m0_floor, gs, gc, direct, flag, st)
+                       : launch_bwd_mfma_mx(w_dt, dY, Xc, Xs, M, N, K, p.chunk, p.splits, W, s_fp, c, sb, ste_clip,
+                                            e8m0_floor, gs, gc, direct, flag, st);
     if (e != hipSuccess || direct) return e;
     const int64_t total = N * (nb + ns);
     const unsigned g = (unsigned)std::min<int64_t>(std::max<int64_t>(cdiv(total, 256), 1), kStreamGridCap);

@@ -160,6 +160,11 @@ hipError_t launch_fwd_mfma(const void *X, const void *W, int64_t M, int64_t N, i
 // the forward on 128 x 128 tiles: bf16 operands (Xs == nullptr) or packed MXFP4
 hipError_t launch_fwd_small(const void *X, const void *W, const void *Xs, const void *Ws, int64_t M, int64_t N, int64_t K,
                             const void *Yref, void *dY, float dscale, double *colpart, hipStream_t st);
+// the backward on 128 x 128 tiles: X is bf16 X_hat (Xs == nullptr) or the packed MXFP4 codes
+hipError_t launch_bwd_small(int fmt, int w_dt, const void *dY, const void *X, const void *Xs, int64_t M, int64_t N, int64_t K,
+                            int64_t chunk, int64_t splits, const void *W, const float *s_fp, const float *c, int sb,
+                            const float *alpha, int ste_clip, int e8m0_floor, float *part_s, float *part_c, int direct,
+                            uint32_t *flag, hipStream_t st);
 // dX_hat = dY W_hat (bf16); with splits > 1 through `splits` x [M][K] fp32 sums in `part`
 bool mfma_dx_supported(int64_t M, int64_t N, int64_t K);
 hipError_t launch_dx_mfma(const void *dY, const void *W, int64_t M, int64_t N, int64_t K, int64_t chunk, int64_t splits,

@@ -218,6 +218,196 @@ fwd_small_kernel(const void *__restrict__ X, const void *__restrict__ W, const u
     if (t < kT && n0 + t < N) colpart[(int64_t)tm * N + n0 + t] = red[0][t] + red[1][t];
 }
 
+// ------------------------------------------------------------------------------------------------
+// Backward (see bwd_mfma_kernel and bwd_mfma_mx_kernel): G^T = X_hat^T dY over one split's tokens, 32 per step,
+// operands token-major in [32][128] bf16 tiles (256-byte rows, the 16-byte chunk index xor-ed with 4 (row % 4)).
+constexpr int kRowB = kT * 2, kBOp = 32 * kRowB;  // 8 KB per operand and step
+
+__device__ __forceinline__ uint32_t small_off(uint32_t r, uint32_t c) {
+    return r * (uint32_t)kRowB + (((c >> 3) ^ ((r & 3u) << 2)) << 4) + (c & 7u) * 2u;
+}
+
+// Per-lane byte offset of the lower transposing read of the fragment at columns c (see ds_read_tr)
+__device__ __forceinline__ uint32_t small_tr_off(uint32_t c, int lane) {
+    const uint32_t j = lane & 15;
+    return small_off(8 * (lane >> 5) + (j >> 2), c + 16 * ((lane >> 4) & 1) + 4 * (j & 3));
+}
+
+// A step's fragments, [half][32 columns]: 16 transposing reads and their wait in one block
+struct BwdStepFrags {
+    i16x4_t a[2][2][2], b[2][2][2];  // [half][columns][tokens + 0, + 4]
+};
+__device__ __forceinline__ void read_step_tr(BwdStepFrags &f, uint32_t a0, uint32_t a1, uint32_t b0, uint32_t b1) {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %16\n\tds_read_b64_tr_b16 %1, %16 offset:1024\n\t"
+        "ds_read_b64_tr_b16 %8, %18\n\tds_read_b64_tr_b16 %9, %18 offset:1024\n\t"
+        "ds_read_b64_tr_b16 %2, %17\n\tds_read_b64_tr_b16 %3, %17 offset:1024\n\t"
+        "ds_read_b64_tr_b16 %10, %19\n\tds_read_b64_tr_b16 %11, %19 offset:1024\n\t"
+        "ds_read_b64_tr_b16 %4, %16 offset:4096\n\tds_read_b64_tr_b16 %5, %16 offset:5120\n\t"
+        "ds_read_b64_tr_b16 %12, %18 offset:4096\n\tds_read_b64_tr_b16 %13, %18 offset:5120\n\t"
+        "ds_read_b64_tr_b16 %6, %17 offset:4096\n\tds_read_b64_tr_b16 %7, %17 offset:5120\n\t"
+        "ds_read_b64_tr_b16 %14, %19 offset:4096\n\tds_read_b64_tr_b16 %15, %19 offset:5120\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(f.a[0][0][0]), "=&v"(f.a[0][0][1]), "=&v"(f.a[0][1][0]), "=&v"(f.a[0][1][1]), "=&v"(f.a[1][0][0]),
+          "=&v"(f.a[1][0][1]), "=&v"(f.a[1][1][0]), "=&v"(f.a[1][1][1]), "=&v"(f.b[0][0][0]), "=&v"(f.b[0][0][1]),
+          "=&v"(f.b[0][1][0]), "=&v"(f.b[0][1][1]), "=&v"(f.b[1][0][0]), "=&v"(f.b[1][0][1]), "=&v"(f.b[1][1][0]),
+          "=&v"(f.b[1][1][1])
+        : "v"(a0), "v"(a1), "v"(b0), "v"(b1)
+        : "memory");
+}
+
+// A thread's 8 code bytes and scale byte, read and waited for in one block
+__device__ __forceinline__ void read_codes(uint32_t codes, uint32_t scale, u32x2_t &w, uint32_t &sb) {
+    asm volatile("ds_read_b64 %0, %2\n\tds_read_u8 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(w), "=&v"(sb)
+                 : "v"(codes), "v"(scale)
+                 : "memory");
+}
+
+// With MX, X_hat is packed MXFP4 (Xc codes [M][K / 2], Xs bytes [K / 32][M]): a stage brings the dY tile, the codes
+// ([32 tokens][64 bytes]) and the scale bytes ([4 blocks][32 tokens], one copy per wave), and a step before its use each
+// thread converts 16 codes of the rows its own wave brought into one of two bf16 A stages. 2,048 x 1,024 x 2,560:
+// bf16 26 us, packed 30 with the finishing kernel; on 256 x 256 tiles 39 and 40, most of it their epilogue.
+template <int FMT, int WDT, bool MX>
+__global__ void __launch_bounds__(kThreads, 2)
+bwd_small_kernel(const uint16_t *__restrict__ dY, const void *__restrict__ X, const uint8_t *__restrict__ Xs, int64_t M,
+                 int64_t N, int64_t K, int64_t chunk, const void *__restrict__ W, const float *__restrict__ s_fp,
+                 const float *__restrict__ c, int sb_log2, const float *__restrict__ alpha_ptr, int ste_clip,
+                 int e8m0_floor, float *__restrict__ part_s, float *__restrict__ part_c, int direct, uint32_t *flag,
+                 int tiles_n) {
+    constexpr int S = 4, kStep = 32;
+    constexpr int kXOff = kBOp;                                   // X tile (or codes) after the dY tile
+    constexpr int kScOff = kXOff + 32 * 64;                       // MX: the scale bytes, 256 bytes per wave
+    constexpr int kStage = MX ? kScOff + 4 * 256 : 2 * kBOp;
+    constexpr int kAOff = S * kStage;                             // MX: two bf16 stages of X
+    constexpr int kLds = std::max(kAOff + (MX ? 2 * kBOp : 0), 64 * 1024);
+    constexpr int kLoads = MX ? 5 : 4;
+    __shared__ __attribute__((aligned(16))) char smem[kLds];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const uint32_t id = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+    const uint32_t tile = id % gridDim.x;
+    const int64_t k0 = (int64_t)(tile / (uint32_t)tiles_n) * kT, n0 = (int64_t)(tile % (uint32_t)tiles_n) * kT;
+    const int64_t split = id / gridDim.x;
+    const int64_t t_begin = split * chunk, t_end = std::min<int64_t>(M, t_begin + chunk);
+    const int64_t nk = t_end > t_begin ? (t_end - t_begin + kStep - 1) / kStep : 0;
+    lds_char *const lsm = (lds_char *)smem;
+    // A 16-byte load instruction fills 4 token rows: lane L lands in row 4 q + L / 16, physical chunk L % 16 of block q;
+    // a wave fills blocks 2 w and 2 w + 1. Columns past the matrix get bit 31; rows past the token range lie outside the
+    // step's resource.
+    auto tile_offs = [&](int64_t C, int64_t c0, uint32_t (&off)[2]) {
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const uint32_t row = 4u * (2u * wave_u + i) + ((uint32_t)lane >> 4);
+            const uint32_t col = (uint32_t)c0 + (((uint32_t)lane & 15u) ^ ((row & 3u) << 2)) * 8u;
+            off[i] = ((row * (uint32_t)C + col) * 2u) | (uint32_t)(col >= (uint32_t)C) << 31;
+        }
+    };
+    uint32_t y_off[2], x_off[2];
+    tile_offs(N, n0, y_off);
+    if constexpr (!MX) tile_offs(K, k0, x_off);
+    // MX: 4-byte loads; a wave fills code rows 8 w .. 8 w + 7 (four per instruction) and its own scale bytes (lanes 0-31:
+    // block L / 8, tokens 4 (L % 8) .. + 3)
+    const int64_t kc = K / 2;
+    const uint32_t c_col = (uint32_t)(k0 / 2) + 4u * ((uint32_t)lane & 15u);
+    const uint32_t c_bad = (uint32_t)(c_col >= (uint32_t)kc) << 31;
+    const uint32_t s_blk = (uint32_t)(k0 / 32) + ((uint32_t)lane >> 3);
+    const uint32_t s_off = s_blk * (uint32_t)M + 4u * ((uint32_t)lane & 7u);
+    const uint32_t s_bad = (uint32_t)(lane >= 32 || s_blk >= (uint32_t)(K / 32)) << 31;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(Xs, MX ? (K / 32) * M : 0);
+    auto issue = [&](int64_t j, int s) {
+        const int64_t t0 = t_begin + j * kStep, rem = t_end - t0;
+        const int64_t rows = rem <= 0 ? 0 : (rem < kStep ? rem : kStep), tb = rows ? t0 : 0;
+        lds_char *const st = lsm + s * kStage;
+        const __amdgpu_buffer_rsrc_t ry = make_rsrc(dY + tb * N, rows * N * 2);
+        if constexpr (MX) {
+            const __amdgpu_buffer_rsrc_t rc = make_rsrc(static_cast<const uint8_t *>(X) + tb * kc, rows * kc);
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                const uint32_t blk = 2u * wave_u + i, row = 4u * blk + ((uint32_t)lane >> 4);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, st + kXOff + blk * 256, 4,
+                                                         (int)((row * (uint32_t)kc + c_col) | c_bad), 0, 0, 0);
+            }
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, st + kScOff + wave_u * 256, 4,
+                                                     (int)((s_off + (uint32_t)t0) | s_bad | (rows ? 0u : 0x80000000u)), 0, 0, 0);
+        } else {
+            const __amdgpu_buffer_rsrc_t rx = make_rsrc(static_cast<const uint16_t *>(X) + tb * K, rows * K * 2);
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, st + kXOff + (2 * wave_u + i) * 1024, 16, (int)x_off[i], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ry, st + (2 * wave_u + i) * 1024, 16, (int)y_off[i], 0, 0, 0);
+    };
+    const uint32_t lds0 = lds_addr(smem);
+    // MX: this thread's codes 16 hb .. + 15 of token row, in the order of the rows that its wave brought
+    const uint32_t row = (uint32_t)t >> 3, hb = (uint32_t)t & 7u;
+    const uint32_t cv_dst0 = small_off(row, 16u * hb), cv_dst1 = small_off(row, 16u * hb + 8u);
+    auto convert = [&](int s, int as) {
+        u32x2_t w;
+        uint32_t sb;
+        const uint32_t st = lds0 + (uint32_t)s * kStage;
+        read_codes(st + kXOff + row * 64u + 8u * hb, st + kScOff + (uint32_t)wave_u * 256u + 32u * (hb >> 1) + row, w, sb);
+        const float scale = exp2i((int)sb - 127);
+        u32x4_t v[2];
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            v[h].x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w[h], scale, 0));
+            v[h].y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w[h], scale, 1));
+            v[h].z = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w[h], scale, 2));
+            v[h].w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w[h], scale, 3));
+        }
+        const uint32_t ab = lds0 + kAOff + (uint32_t)as * kBOp;
+        asm volatile("ds_write_b128 %0, %1\n\tds_write_b128 %2, %3" : : "v"(ab + cv_dst0), "v"(v[0]), "v"(ab + cv_dst1), "v"(v[1]) : "memory");
+    };
+    uint32_t a_off[2], b_off[2];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        a_off[i] = small_tr_off(wm * 64 + i * 32, lane);
+        b_off[i] = small_tr_off(wn * 64 + i * 32, lane);
+    }
+    f32x16_t acc[2][2];
+    const f32x16_t zero = {};
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) acc[i][j] = zero;
+#pragma unroll
+    for (int s = 0; s < S - 1; s++) issue(s, s);
+    if constexpr (MX) {
+        FOCUS_WAIT_VMCNT(kLoads * (S - 2));  // this wave's own rows of slot 0
+        asm volatile("" ::: "memory");
+        convert(0, 0);
+    }
+    for (int64_t kt = 0; kt < nk; kt++) {
+        const int sc = (int)(kt & (S - 1));
+        // slot kt (MX: and kt + 1, whose codes are converted now) has landed here, and this thread's conversion of slot
+        // kt is written; after the barrier everyone's, and every wave is done with step kt - 1's stages
+        FOCUS_WAIT_VMCNT(kLoads * (MX ? S - 3 : S - 2));
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        const uint32_t st = lds0 + (uint32_t)sc * kStage;
+        const uint32_t ab = MX ? lds0 + kAOff + (uint32_t)(kt & 1) * kBOp : st + kXOff;
+        BwdStepFrags f;
+        read_step_tr(f, ab + a_off[0], ab + a_off[1], st + b_off[0], st + b_off[1]);
+        issue(kt + S - 1, (sc + S - 1) & (S - 1));
+        static_for<2>([&](auto h) {
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+#pragma unroll
+                for (int j = 0; j < 2; j++) {
+                    const i16x4_t va[2] = {f.a[h][i][0], f.a[h][i][1]}, vb[2] = {f.b[h][j][0], f.b[h][j][1]};
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, va),
+                                                                        __builtin_bit_cast(bf16x8_t, vb), acc[i][j], 0, 0, 0);
+                }
+        });
+        if constexpr (MX) convert((sc + 1) & (S - 1), (int)((kt + 1) & 1));
+    }
+    FOCUS_WAIT_VMCNT(0);  // the empty slots' zero writes must land before the LDS is used again
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    ste_epilogue<FMT, WDT, kT>(acc, k0, n0, split, N, K, W, s_fp, c, sb_log2, alpha_ptr, ste_clip, e8m0_floor, part_s,
+                               part_c, direct, flag, smem);
+}
+
 }  // namespace
 
 hipError_t launch_fwd_small(const void *X, const void *W, const void *Xs, const void *Ws, int64_t M, int64_t N, int64_t K,
@@ -231,6 +421,24 @@ hipError_t launch_fwd_small(const void *X, const void *W, const void *Xs, const 
     if (Xs) { if (Yref) FS(true, true); else FS(false, true); }
     else { if (Yref) FS(true, false); else FS(false, false); }
 #undef FS
+    return hipGetLastError();
+}
+
+hipError_t launch_bwd_small(int fmt, int w_dt, const void *dY, const void *X, const void *Xs, int64_t M, int64_t N, int64_t K,
+                            int64_t chunk, int64_t splits, const void *W, const float *s_fp, const float *c, int sb,
+                            const float *alpha, int ste_clip, int e8m0_floor, float *part_s, float *part_c, int direct,
+                            uint32_t *flag, hipStream_t st) {
+    const int tiles_k = (int)((K + kT - 1) / kT), tiles_n = (int)((N + kT - 1) / kT);
+    int sbl = 0;
+    while ((1 << sbl) < sb) sbl++;
+    const dim3 grid((unsigned)tiles_k * tiles_n, (unsigned)splits);
+    const uint16_t *dy = static_cast<const uint16_t *>(dY);
+    const uint8_t *xs = static_cast<const uint8_t *>(Xs);
+#define BS(F, WD, MX) bwd_small_kernel<F, WD, MX><<<grid, kThreads, 0, st>>>(dy, X, xs, M, N, K, chunk, W, s_fp, c, sbl, alpha, ste_clip, e8m0_floor, part_s, part_c, direct, flag, tiles_n)
+    if (xs) { if (w_dt == kBF16) BS(kFmtMX, kBF16, true); else BS(kFmtMX, kF32, true); }
+    else if (fmt == kFmtMX) { if (w_dt == kBF16) BS(kFmtMX, kBF16, false); else BS(kFmtMX, kF32, false); }
+    else { if (w_dt == kBF16) BS(kFmtNV, kBF16, false); else BS(kFmtNV, kF32, false); }
+#undef BS
     return hipGetLastError();
 }
 

@@ -50,6 +50,7 @@ struct FwdPlan {
 // `chunk` tokens per split; partial gradient sums [splits][N][K/B] and [splits][N][K/sb] (float).
 struct BwdPlan {
     int path;
+    int tile;       // edge of a G tile
     int64_t splits;
     int64_t chunk;
     size_t ws_bytes;

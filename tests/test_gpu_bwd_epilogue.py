@@ -4,10 +4,10 @@
 The operands are small integers, so G = dY^T X is exact in fp32 whatever the order of its sums, and the
 two calls differ by the order (and fused multiply-adds) of at most 32 products: each is within 33 roundings
 of 2^-24 of the sum of its terms' magnitudes, and the last division or product adds two. Where the
-tokens are split (up to 4 ranges here), the terms are those of each range's own G, whose magnitudes
-|dY|^T |X| bounds, and the ranges' sums add up to 4 roundings, so the difference is below 2 * 39 * 2^-24
-times the sum formed with |dY|^T |X|. Sizes lie at the edges of the 256 x 256 tile, with one
-token range (the gradients written by the kernel itself) and with several; scales inside the fast
+tokens are split (up to 8 ranges here), the terms are those of each range's own G, whose magnitudes
+|dY|^T |X| bounds, and the ranges' sums add up to 8 roundings, so the difference is below 2 * 43 * 2^-24
+times the sum formed with |dY|^T |X|. Sizes lie at the edges of the 128 x 128 and 256 x 256 tiles (the last size takes the large ones), with one
+token range (the gradients written by the kernel itself) and with several, at a ragged number of 32-token steps; scales inside the fast
 division's range, outside it, and zero.
 """
 import pytest
@@ -31,7 +31,8 @@ def F():
     (NV, 8, torch.bfloat16, 1, "normal"), (NV, 16, torch.bfloat16, 0, "zero"), (NV, 4, torch.float32, 1, "zero"),
     (NV, 2, torch.bfloat16, 1, "normal"),
 ])
-@pytest.mark.parametrize("M,N,K", [(20, 8, 32), (70, 256, 256), (36, 264, 544), (1040, 520, 288)])
+@pytest.mark.parametrize("M,N,K", [(20, 8, 32), (70, 256, 256), (36, 264, 544), (1040, 520, 288), (100, 136, 112 * 16),
+                                   (5076, 3000, 1664)])
 def test_epilogue_matches_streaming_backward(F, fmt, sb, wdt, clip, scale, M, N, K):
     announce(f"bwd epilogue fmt={fmt} sb={sb} {wdt} clip={clip} {scale} {M}x{N}x{K}")
     g = torch.Generator().manual_seed(M * 7 + N + K)
@@ -61,6 +62,6 @@ def test_epilogue_matches_streaming_backward(F, fmt, sb, wdt, clip, scale, M, N,
     u = (W.double().abs().view(N, -1, block) / low.clamp(min=1e-300)[..., None]).clamp(max=6.0 if clip else 1e300)
     u = torch.where(low[..., None] > 0, u, torch.zeros_like(u))
     mag = (Ga.view(N, -1, block) * (6.0 + u)).sum(2) * (float(alpha) if fmt == NV else 1.0)
-    assert bool(((gs.double() - rs.double()).abs() <= 78 * 2.0 ** -24 * mag).all())
+    assert bool(((gs.double() - rs.double()).abs() <= 86 * 2.0 ** -24 * mag).all())
     mag = (Ga * W.double().abs()).view(N, -1, sub).sum(2) / (c.double() ** 2 if sb else 1.0)
-    assert bool(((gc.double() - rc.double()).abs() <= 78 * 2.0 ** -24 * mag).all())
+    assert bool(((gc.double() - rc.double()).abs() <= 86 * 2.0 ** -24 * mag).all())
