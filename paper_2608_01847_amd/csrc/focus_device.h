@@ -197,7 +197,7 @@ __device__ __forceinline__ Quantized quantize_element(float x, float sq, float s
 // overflow and underflow, which holds when 2^-40 <= b <= 2^40, |a| <= 2^80 and |a / b| >= 2^-4. Below
 // 2^-4 the result stays within a few units of the last place of a / b, far under the smallest E2M1
 // midpoint (0.25), with the sign of a; zeros keep their sign. Callers take this path only when every
-// lane's operands are in that range (scale_in_fast_range, and a finite bf16 weight of at most 2^80).
+// lane's operands are in that range (scale_in_fast_range, and a finite weight of at most 2^80).
 __device__ __forceinline__ float div_by_scale(float a, float b, float y) {
     const float q0 = a * y;
     const float r0 = __builtin_fmaf(q0, b, -a);
