@@ -169,7 +169,10 @@ bwd_valu_kernel(const void *__restrict__ dY, const void *__restrict__ X, int64_t
 
 // col_sq[n] = sum over m-tiles of colpart[mt][n] in a fixed order: 16 row groups (mt mod 16, each
 // summed in ascending mt), then a fixed pairwise tree over the groups. A workgroup covers 16
-// columns, so even a narrow layer spreads over many workgroups.
+// columns, so even a narrow layer spreads over many workgroups. Bound by the latency of its loads (each added before
+// the next was issued): kAhead are in flight at a time, those past the end in bounds and left out.
+// Partials of 256 x 9,728: 10.9 -> 8.2 us, of 256 x 2,560: 10.0 -> 4.8; the loss of 9,728 columns: 11.3 -> 4.6.
+constexpr int kAhead = 8;
 __global__ void __launch_bounds__(256)
 colsum_kernel(const double *__restrict__ colpart, int64_t mtiles, int64_t N, double *__restrict__ col_sq) {
     __shared__ double red[16][16];
@@ -177,7 +180,13 @@ colsum_kernel(const double *__restrict__ colpart, int64_t mtiles, int64_t N, dou
     const int64_t n = (int64_t)blockIdx.x * 16 + cx;
     double s = 0.0;
     if (n < N)
-        for (int64_t mt = grp; mt < mtiles; mt += 16) s += colpart[mt * N + n];
+        for (int64_t m0 = grp; m0 < mtiles; m0 += 16 * kAhead) {
+            double v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; u++) v[u] = colpart[std::min<int64_t>(m0 + 16 * u, mtiles - 1) * N + n];
+#pragma unroll
+            for (int u = 0; u < kAhead; u++) s += m0 + 16 * u < mtiles ? v[u] : 0.0;
+        }
     red[grp][cx] = s;
     __syncthreads();
     for (int w = 8; w > 0; w >>= 1) {
@@ -192,7 +201,13 @@ __global__ void __launch_bounds__(256)
 loss_kernel(const double *__restrict__ col_sq, int64_t N, double inv_mn, double *__restrict__ loss) {
     __shared__ double red[256];
     double s = 0.0;
-    for (int64_t n = threadIdx.x; n < N; n += 256) s += col_sq[n];
+    for (int64_t n0 = threadIdx.x; n0 < N; n0 += 256 * kAhead) {
+        double v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; u++) v[u] = col_sq[std::min<int64_t>(n0 + 256 * u, N - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; u++) s += n0 + 256 * u < N ? v[u] : 0.0;
+    }
     red[threadIdx.x] = s;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
