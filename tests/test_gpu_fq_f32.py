@@ -1,6 +1,7 @@
-"""Fake quantisation of fp32 weights on the E2M1 decision points, bit-exact.
+"""Fake quantisation of fp32 weights on the E2M1 decision points, and the NVFP4 activation pass on both sides of the
+size from which its tensor scale is folded by a launch of its own; all bit-exact.
 
-Each sub-block places one weight whose quotient W / S_q (Eq. 7, 8) lies within +-3 units in the last place
+fp32 weights: each sub-block places one weight whose quotient W / S_q (Eq. 7, 8) lies within +-3 units in the last place
 of a rounding midpoint of E2M1 or of 6. Other rows leave the range of the reciprocal: non-finite, huge and subnormal
 weights, scales outside [2^-40, 2^40], zero scales. Codes, scale bytes and W_hat against the oracle.
 """
@@ -60,3 +61,23 @@ def test_fp32_weights_on_decision_points(fmt, sb):
             assert_bits_equal(sbytes.cpu().numpy(), ref_bytes, f"scale bytes (layout {layout})")
             assert_bits_equal(host_bits32(w32), fq.w_hat.view(np.uint32), "W_hat fp32")
             assert_bits_equal(host_bits16(w16), O.bf16_bits(O.bf16_round(fq.w_hat)), "W_hat bf16")
+
+
+# 2,048 workgroups fold the partial maxima themselves; one row of workgroups more, and a launch does it once
+@pytest.mark.parametrize("dtype,rows,more", [(torch.bfloat16, 16384, 1), (torch.float32, 2048, 1), (torch.float32, 3, 0)])
+@pytest.mark.parametrize("fill", ["normal", "zeros"])
+def test_tensor_scale_is_the_same_on_both_sides_of_the_fold(dtype, rows, more, fill):
+    F = require_gpu()
+    announce(f"nvfp4 activations {dtype} {rows} and {rows + more} x 2048, {fill}")
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    X = torch.zeros(rows + more, 2048, device="cuda", dtype=dtype)
+    if fill == "normal":
+        X.copy_(torch.randn(X.shape, generator=g, device="cuda"))
+        X[rows // 2, 77] = -9.5
+        X[rows:] *= 0.5
+    a = F.fakequant_fwd(X, 1, want_codes=True, want_scale_bytes=True, want_alpha=True)
+    b = F.fakequant_fwd(X[:rows].contiguous(), 1, want_codes=True, want_scale_bytes=True, want_alpha=True)
+    for p, q in zip(a[:3], b[:3]):
+        assert torch.equal(p[:rows], q)
+    want = np.float32(9.5) / np.float32(2688.0) if fill == "normal" else np.float32(1.0)
+    assert a[3].item() == want and b[3].item() == want
