@@ -12,6 +12,8 @@
 // register r of lane l holds C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]. The reduction index may be
 // permuted alike in both operands: the forward's lanes read 16 bytes (4 k) of their row and half, so
 // instruction s of a group of 8 k multiplies k = s and k = 4 + s.
+#include <type_traits>
+
 #include "gemm_common.h"
 
 namespace focus {
@@ -61,8 +63,12 @@ __device__ __forceinline__ F32Cols read_cols_f32(uint32_t a, uint32_t b) {
 //   T == 64: 64 x 64 tile, the waves 2 x 2; a step is 32 k (two such tiles per operand), three stages of
 //            16 KB, one barrier per step.
 //   T == 32: 32 x 32 tile, the waves taking every fourth 16 k each, in four stages of their own (no
-//            barrier in the loop), their sums added in a fixed order through LDS. For outputs too small to
-//            fill the chip with 64 x 64 tiles: four times the workgroups, a quarter of the serial steps.
+//            barrier in the loop). For outputs too small to fill the chip with 64 x 64 tiles: four times the
+//            workgroups, a quarter of the serial steps. Each wave keeps four accumulators in turn, so a chain
+//            of roundings is K / 16 products long, and the 16 sums are added, and Y_ref subtracted, in fp64. A
+//            gradient's largest error comes from the outputs with one very large term, at whose size every
+//            later addition rounds: with one accumulator and fp32 sums 1.4e-5 of the gradients' root mean
+//            square (128 x 256 x 256, NVFP4, Student-t activations), 2.4e-6 so, in the same time.
 template <bool MSE, int T>
 __global__ void __launch_bounds__(256)
 fwd_f32_kernel(const float *__restrict__ X, const float *__restrict__ W, int64_t M, int64_t N, int64_t K,
@@ -106,7 +112,8 @@ fwd_f32_kernel(const float *__restrict__ X, const float *__restrict__ W, int64_t
             __builtin_amdgcn_raw_ptr_buffer_load_lds(op ? rw : rx, dst, 16, (int)off, 0, 0, 0);
         }
     };
-    f32x16_t acc = {};
+    constexpr int kAcc = kSplit ? 4 : 1;  // accumulators, taking the instructions in turn
+    f32x16_t acc[kAcc] = {};
     // this lane's 16-byte chunks lh and 2 + lh of its rows of a 16-k tile of A and B
     const uint32_t lds0 = (uint32_t)(uintptr_t)lsm + (kSplit ? (uint32_t)wave_u * S * kStage : 0u);
     const uint32_t a0 = fwd_off(wm * 32 + lr, lh), a1 = fwd_off(wm * 32 + lr, 2 + lh);
@@ -115,7 +122,7 @@ fwd_f32_kernel(const float *__restrict__ X, const float *__restrict__ W, int64_t
         const F32Frags f = read_frags_f32(as + a0, as + a1, bs + b0, bs + b1);
 #pragma unroll
         for (int e = 0; e < 8; e++)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[e / 4][e % 4], f.b[e / 4][e % 4], acc, 0, 0, 0);
+            acc[e % kAcc] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[e / 4][e % 4], f.b[e / 4][e % 4], acc[e % kAcc], 0, 0, 0);
     };
 #pragma unroll
     for (int s = 0; s < S - 1; s++) issue(s, s);
@@ -142,22 +149,23 @@ fwd_f32_kernel(const float *__restrict__ X, const float *__restrict__ W, int64_t
     __syncthreads();
     // ---- epilogue: this wave's registers r0 .. r0 + R - 1 of the tile's accumulator ----
     constexpr int R = kSplit ? 4 : 16;
-    float o[R];
+    typename std::conditional<kSplit, double, float>::type o[R];
     if constexpr (kSplit) {
-        float *part = reinterpret_cast<float *>(smem);  // [wave][register][lane]
+        double *part = reinterpret_cast<double *>(smem);  // [wave][register][lane]
 #pragma unroll
-        for (int r = 0; r < 16; r++) part[(wave * 16 + r) * 64 + lane] = acc[r];
+        for (int r = 0; r < 16; r++)
+            part[(wave * 16 + r) * 64 + lane] = ((double)acc[0][r] + (double)acc[1][r]) + ((double)acc[2][r] + (double)acc[3][r]);
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-            float s = 0.0f;
+            double s = 0.0;
 #pragma unroll
             for (int w = 0; w < 4; w++) s += part[(w * 16 + wave * 4 + r) * 64 + lane];
             o[r] = s;
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < 16; r++) o[r] = acc[r];
+        for (int r = 0; r < 16; r++) o[r] = acc[0][r];
     }
     const int64_t n = n0 + wn * 32 + lr;
     const bool n_ok = n < N;
@@ -176,11 +184,11 @@ fwd_f32_kernel(const float *__restrict__ X, const float *__restrict__ W, int64_t
         const int64_t m = row_of(r);
         if (n_ok && m < M) {
             if constexpr (MSE) {
-                const float d = o[r] - y[r];
+                const float d = (float)(o[r] - y[r]);
                 dY[m * N + n] = d * dscale;
                 csum += (double)d * (double)d;
             } else {
-                dY[m * N + n] = o[r];
+                dY[m * N + n] = (float)o[r];
             }
         }
     }
