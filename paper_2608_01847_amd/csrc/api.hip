@@ -106,7 +106,8 @@ focus_status check_fwd_mx_args(const uint8_t *X_codes, const uint8_t *X_scales, 
 // ---- fixed device scratch of the allocation-free forward ---------------------------------------
 // 32 MiB per GPU: the kWsHeader bytes the workspace layout skips, ceil(M / 256) x N partial sums of
 // D^2 (fp64) and, when the caller passes no col_sq, N column sums. Every hidden-2560 layer at 65,536
-// tokens fits (at most 20 MB).
+// tokens fits (at most 20 MB). (Where the forward takes 128 x 128 tiles there are at most 512 of them,
+// 0.5 MB of sums.)
 constexpr size_t kNoAllocScratchBytes = size_t(32) << 20;
 
 size_t noalloc_fwd_scratch_bytes(int64_t M, int64_t N, bool have_col_sq) {

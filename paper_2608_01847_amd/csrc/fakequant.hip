@@ -9,7 +9,7 @@
 
 namespace focus {
 
-// xor-shuffle within groups of `width` lanes (width <= 4 here); every lane of the group is active
+// xor-shuffle; every lane of the group is active
 __device__ __forceinline__ float shfl_xor_f(float v, int mask) { return __shfl_xor(v, mask, 64); }
 
 __device__ __forceinline__ float group_max(float v, int lanes) {
