@@ -6,7 +6,7 @@
 // with direct-to-LDS buffer loads, some steps ahead. A workgroup is four waves, one 32 x 32 accumulator
 // (16 registers) each; three workgroups fit a CU, whose waves hide each other's waits. 2,037 x 1,001 x
 // 1,504: forward 68.7 us, backward 69.9 us (89 TFLOP/s), where 4 x 4 register tiles of scalar FMAs from
-// 4-byte loads took 231 and 253; 128 x 256 x 256: 5.4 and 5.7 us, before 42.1 and 22.6.
+// 4-byte loads took 231 and 253; 128 x 256 x 256: 5.9 and 5.9 us, before 42.1 and 22.6.
 //
 // Operand layout of 32x32x2: lane l holds A[l % 32][l / 32] (resp. B[l / 32][l % 32]); accumulator
 // register r of lane l holds C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]. The reduction index may be
@@ -68,7 +68,7 @@ __device__ __forceinline__ F32Cols read_cols_f32(uint32_t a, uint32_t b) {
 //            of roundings is K / 16 products long, and the 16 sums are added, and Y_ref subtracted, in fp64. A
 //            gradient's largest error comes from the outputs with one very large term, at whose size every
 //            later addition rounds: with one accumulator and fp32 sums 1.4e-5 of the gradients' root mean
-//            square (128 x 256 x 256, NVFP4, Student-t activations), 2.4e-6 so, in the same time.
+//            square (128 x 256 x 256, NVFP4, Student-t activations), 2.4e-6 so (5.9 us for 5.4).
 template <bool MSE, int T>
 __global__ void __launch_bounds__(256)
 fwd_f32_kernel(const float *__restrict__ X, const float *__restrict__ W, int64_t M, int64_t N, int64_t K,
