@@ -311,45 +311,54 @@ BwdPlan plan_bwd(int op_dt, int fmt, int sb, int64_t M, int64_t N, int64_t K, bo
     BwdPlan p;
     p.path = op_dt == kBF16 ? (!want_G && mfma_bwd_supported(M, N, K) ? 1 : 0) : (f32_bwd_supported(M, N, K) ? 2 : 0);
     p.tile = p.path == 1 ? kMfmaTileN : 64;
-    const int64_t tn = p.tile, tk = p.tile;
     const int64_t step = p.path == 1 ? kMfmaTokenStep : (p.path == 2 ? kF32TokenStep : 16);
-    const int64_t tiles = cdiv(N, tn) * cdiv(K, tk);
+    const int64_t tiles = cdiv(N, p.tile) * cdiv(K, p.tile);
     const int64_t steps_total = cdiv(std::max<int64_t>(M, 1), step);
+    const int64_t nb = K / block_of(fmt), ns = K / sb, sums = N * (nb + ns);  // sums of one split
     int64_t splits = 1;
     if (!want_G) {
-        // The token range is split so that tiles * splits workgroups fill the chip in whole rounds
-        // (one 256 x 256 workgroup per CU on the MFMA path, several 64 x 64 ones on the VALU path):
-        // minimise rounds * (steps per split + epilogue), each split keeping >= 4 steps (fp32: 1). The MFMA
-        // path's straight-through epilogue (a 256 x 256 tile at one wave per SIMD) costs about as
-        // much as 20 of its 64-token steps: of 4 to 36, 16 to 20 gave the best splits on layers of 2,048 to
-        // 65,536 tokens (the others up to 2% slower).
-        // On the fp32 path a CU's matrix units are busy with one workgroup, so workgroups queue per CU too;
-        // its epilogue (64 x 64) costs about 3 of its 32-token steps.
+        // The token range is split so that tiles * splits workgroups fill the chip in whole rounds (one 256 x 256
+        // workgroup per CU on the MFMA path, several 64 x 64 ones on the VALU path): minimise the rounds, each the
+        // steps of a split and an epilogue, and what splits cost beside them. Each split keeps >= 4 steps (fp32: 1).
+        //  * MFMA path, in units of 0.02 us (190 layers of 512 to 131,072 tokens, each at up to 16 tilings and split
+        //    counts): a 64-token step of a 256 x 256 tile 70, its epilogue 1040; more than one split a finishing
+        //    launch (3 us) and its fp32 sums written and read once (3 TB/s). More splits have to promise 2% more than
+        //    fewer, near ties went the other way (11,004 x 8,096 x 1,408: 241 us with one split, 263 with four).
+        //  * fp32 path: a CU's matrix units are busy with one workgroup, so workgroups queue per CU too; its epilogue
+        //    (64 x 64) costs about 3 of its 32-token steps (0.75 us each), the sums as above. Tiles that make 16
+        //    rounds by themselves are not split (the last round is then a sixteenth of the time at most).
+        // A cost is at least tiles * (steps_total * step + s * epilogue) / slots: past the best one the search ends.
         const int64_t slots = p.path == 0 ? 2048 : kMfmaConcurrentWgs;
-        const int64_t epilogue_steps = p.path == 1 ? 20 : (p.path == 2 ? 3 : 4);
-        const int64_t min_steps = p.path == 2 ? 1 : 4;
-        const int64_t max_splits = std::max<int64_t>(1, std::min<int64_t>(steps_total / min_steps, 4096));
+        const int64_t step_cost = p.path == 1 ? 70 : 1, epilogue = p.path == 1 ? 1040 : (p.path == 2 ? 3 : 4);
+        const int64_t launch = p.path == 1 ? 150 : 0, sums_rate = p.path == 1 ? 7500 : (p.path == 2 ? 281250 : 0);
+        const int64_t margin = p.path == 1 ? 2 : 0;  // percent
+        auto beside = [&](int64_t s) { return s > 1 && sums_rate ? launch + s * sums / sums_rate : 0; };
+        const int64_t most = p.path == 2 ? (tiles >= 16 * slots ? 1 : steps_total) : steps_total / 4;
+        const int64_t max_splits = std::max<int64_t>(1, std::min<int64_t>(most, 4096));
         int64_t best = -1;
         for (int64_t s = 1; s <= max_splits; s++) {
-            const int64_t rounds = cdiv(tiles * s, slots);
-            const int64_t cost = rounds * (cdiv(steps_total, s) + epilogue_steps);
-            if (best < 0 || cost < best) {
+            if (best >= 0 && tiles * (step_cost * steps_total + s * epilogue) >= best * slots) break;
+            const int64_t cost = cdiv(tiles * s, slots) * (step_cost * cdiv(steps_total, s) + epilogue) + beside(s);
+            if (best < 0 || cost * (100 + margin) < best * 100) {
                 best = cost;
                 splits = s;
             }
         }
         // MFMA path: 128 x 128 tiles, two workgroups per CU, where the large tiles' epilogue would cost more than they
-        // save. Measured, in units of 0.02 us: a 64-token step takes 73 on a large tile (20 of them the epilogue); on
-        // small ones 45 with one workgroup on the CU and 30 for each of two, the epilogue 400 and 325. (2,048 x
-        // 1,024 x 2,560: 26 to 30 us for 39; 3,001 x 1,368 x 2,128: 39 for 47; 5,076 x 3,000 x 1,664: 79 to 95 for 71.)
+        // save (measured as above): a 64-token step takes 39 with one workgroup on the CU and 53 with two, their
+        // epilogues 316 and 350; MXFP4, whose packed codes the small tiles convert twice as often, 48, 64, 330 and 280
+        // (for its bf16 operands too, whose gradients have the packed ones' bits). (2,048 x 1,024 x 2,560: 26 to 30 us
+        // for 39; 3,001 x 1,368 x 2,128: 39 for 47; 5,076 x 3,000 x 1,664: 79 to 95 for 71.)
         if (p.path == 1) {
             const int64_t small_tiles = cdiv(N, kSmallTile) * cdiv(K, kSmallTile);
-            int64_t best_small = best * 73;
+            const bool mx = fmt == kFmtMX;
+            const int64_t step1 = mx ? 48 : 39, ep1 = mx ? 330 : 316, step2 = mx ? 64 : 53, ep2 = mx ? 280 : 350;
             for (int64_t s = 1; s <= std::max<int64_t>(1, steps_total / 2) && small_tiles * s <= 8 * slots; s++) {
+                if (small_tiles * (step2 * steps_total + s * ep2) >= best * 2 * slots) break;
                 const int64_t per_cu = cdiv(small_tiles * s, slots), steps = cdiv(steps_total, s);
-                const int64_t cost = per_cu / 2 * 2 * (30 * steps + 325) + per_cu % 2 * (45 * steps + 400);
-                if (cost < best_small) {
-                    best_small = cost;
+                const int64_t cost = per_cu / 2 * (step2 * steps + ep2) + per_cu % 2 * (step1 * steps + ep1) + beside(s);
+                if (cost * (100 + margin) < best * 100) {
+                    best = cost;
                     splits = s;
                     p.tile = kSmallTile;
                 }
@@ -358,8 +367,7 @@ BwdPlan plan_bwd(int op_dt, int fmt, int sb, int64_t M, int64_t N, int64_t K, bo
     }
     p.chunk = cdiv(steps_total, splits) * step;
     p.splits = std::max<int64_t>(1, cdiv(M, p.chunk));
-    const int64_t nb = K / block_of(fmt), ns = K / sb;
-    p.ws_bytes = kWsHeader + (size_t)(p.splits * N * (nb + ns)) * sizeof(float);
+    p.ws_bytes = kWsHeader + (size_t)(p.splits * sums) * sizeof(float);
     return p;
 }
 
