@@ -3,10 +3,11 @@
 //
 // Bound by the matrix units (256 flop per cycle and CU, twice what separate fp32 FMAs reach without
 // packed instructions) once the operands are staged: operand tiles go from memory straight into LDS
-// with direct-to-LDS buffer loads, some steps ahead. A workgroup is four waves, one 32 x 32 accumulator
-// (16 registers) each; three workgroups fit a CU, whose waves hide each other's waits. 2,037 x 1,001 x
-// 1,504: forward 68.7 us, backward 69.9 us (89 TFLOP/s), where 4 x 4 register tiles of scalar FMAs from
-// 4-byte loads took 231 and 253; 128 x 256 x 256: 5.9 and 5.9 us, before 42.1 and 22.6.
+// with direct-to-LDS buffer loads, some steps ahead. A workgroup is four waves, each a 32 x 32 tile (16 registers
+// per accumulator); three workgroups of 48 KB LDS fit a CU (of the forward's small tile, 65 KB, two), whose waves hide
+// each other's waits. 2,037 x 1,001 x 1,504: forward 65 us, backward 73 us with its finishing launch (84 TFLOP/s),
+// where 4 x 4 register tiles of scalar FMAs from 4-byte loads took 231 and 253; 128 x 256 x 256: 5.9 and 5.9 us,
+// before 42.1 and 22.6.
 //
 // Operand layout of 32x32x2: lane l holds A[l % 32][l / 32] (resp. B[l / 32][l % 32]); accumulator
 // register r of lane l holds C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]. The reduction index may be
@@ -209,13 +210,17 @@ fwd_f32_kernel(const float *__restrict__ X, const float *__restrict__ W, int64_t
 // waves 2 x 2, with the fused straight-through epilogue. A step is 32 tokens ([32][64] floats per operand,
 // three stages of 16 KB); fragments are 4-byte LDS reads of 32 consecutive columns. dY rows start on 4-byte
 // boundaries only unless N % 4 == 0: they are then staged with 4-byte loads (W16 == false).
+// A chain of roundings is 64 tokens long, the chains are added in fp64: with one chain per split the gradients'
+// error against 64 bits was up to 4.4 times that of many short splits (3,507 x 1,758 x 160: 3.1e-7 for 7.0e-8; now
+// 6.4e-8). The additions run beside the next chain's matrix instructions (3,507 x 1,758 x 160 36.9 us for 37.5,
+// 4,096 x 2,048 x 2,048 316 for 306); chains of 32 tokens took 41 and 347, of 128 left some errors above.
 template <int FMT, int WDT, bool W16>
 __global__ void __launch_bounds__(256)
 bwd_f32_kernel(const float *__restrict__ dY, const float *__restrict__ X, int64_t M, int64_t N, int64_t K, int64_t chunk,
                const void *__restrict__ W, const float *__restrict__ s_fp, const float *__restrict__ c, int sb_log2,
                const float *__restrict__ alpha_ptr, int ste_clip, int e8m0_floor, float *__restrict__ part_s,
                float *__restrict__ part_c, int direct, float *__restrict__ G_out, uint32_t *flag, int tiles_k) {
-    constexpr int T = kF32Tile, kStep = kF32TokenStep, S = 3;
+        constexpr int T = kF32Tile, kStep = kF32TokenStep, S = 3;
     constexpr int kOp = kStep * T * 4, kStage = 2 * kOp;  // 8 KB per operand
     constexpr int kLoadsY = W16 ? 2 : 8, kLoads = kLoadsY + 2;
     __shared__ __attribute__((aligned(16))) char smem[S * kStage];
@@ -260,25 +265,53 @@ bwd_f32_kernel(const float *__restrict__ dY, const float *__restrict__ X, int64_
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, st + kOp + blk * 1024, 16, (int)off, 0, 0, 0);
         }
     };
-    f32x16_t acc = {};
+    f32x16_t acc0 = {}, acc1 = {};  // one collects two steps while the other's sums go to gsum, half of them per step
+    double gsum[16] = {};
+    auto fold = [&](const f32x16_t &a, int half) {
+#pragma unroll
+        for (int r = 8 * half; r < 8 * half + 8; r++) gsum[r] += (double)a[r];
+    };
     const uint32_t lds0 = (uint32_t)(uintptr_t)lsm;
     const uint32_t a_off = (uint32_t)(lh * T + wm * 32 + lr) * 4u, b_off = (uint32_t)(lh * T + wn * 32 + lr) * 4u;
 #pragma unroll
     for (int s = 0; s < S - 1; s++) issue(s, s);
     int sc = 0;
-    for (int64_t kt = 0; kt < nk; kt++) {
+    auto step = [&](auto half, int64_t kt, f32x16_t &acc, const f32x16_t &before) {
         FOCUS_WAIT_VMCNT(kLoads * (S - 2));
         asm volatile("s_barrier" ::: "memory");
         const uint32_t as = lds0 + (uint32_t)sc * kStage, bs = as + kOp;
         issue(kt + S - 1, sc == 0 ? S - 1 : sc - 1);  // the stage that every wave was done with at the barrier
+        if (half == 0) acc = f32x16_t{};
 #pragma unroll
         for (int h = 0; h < kStep / 16; h++) {
             const F32Cols f = read_cols_f32(as + a_off + h * 16 * T * 4, bs + b_off + h * 16 * T * 4);
 #pragma unroll
             for (int s = 0; s < 8; s++)
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[s / 2][s % 2], f.b[s / 2][s % 2], acc, 0, 0, 0);
+            if (h == 0) fold(before, half);
         }
         sc = sc == S - 1 ? 0 : sc + 1;
+    };
+    constexpr std::integral_constant<int, 0> lo{};
+    constexpr std::integral_constant<int, 1> hi{};
+    int64_t kt = 0;
+    for (; kt + 4 <= nk; kt += 4) {
+        step(lo, kt, acc0, acc1);
+        step(hi, kt + 1, acc0, acc1);
+        step(lo, kt + 2, acc1, acc0);
+        step(hi, kt + 3, acc1, acc0);
+    }
+    fold(acc1, 0), fold(acc1, 1);
+    acc1 = f32x16_t{};
+    if (kt + 2 <= nk) {
+        step(lo, kt, acc0, acc1);
+        step(hi, kt + 1, acc0, acc1);
+        fold(acc0, 0), fold(acc0, 1);
+        kt += 2;
+    }
+    if (kt < nk) {
+        step(lo, kt, acc0, acc1);
+        fold(acc0, 0), fold(acc0, 1);
     }
     FOCUS_WAIT_VMCNT(0);  // the empty slots' zero writes
     __syncthreads();
@@ -287,7 +320,7 @@ bwd_f32_kernel(const float *__restrict__ dY, const float *__restrict__ X, int64_
     float *const Gs = reinterpret_cast<float *>(smem);  // [64][68]
 #pragma unroll
     for (int r = 0; r < 16; r++)
-        Gs[(wm * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kPitch + wn * 32 + lr] = acc[r];
+        Gs[(wm * 32 + 8 * (r / 4) + 4 * lh + r % 4) * kPitch + wn * 32 + lr] = (float)gsum[r];
     __syncthreads();
     constexpr int B = block_of(FMT);
     const float alpha = FMT == kFmtNV ? *alpha_ptr : 1.0f;

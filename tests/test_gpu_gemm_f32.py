@@ -77,3 +77,17 @@ def test_backward_matches_streaming_backward(F, M, N, K, fmt, sb, wdt, clip, wan
     assert bool(((gs.double() - rs.double()).abs() <= 136 * 2.0 ** -24 * mag).all())
     mag = (Ga * W.double().abs()).view(N, -1, sub).sum(2) / (c.double() ** 2 if sb else 1.0)
     assert bool(((gc.double() - rc.double()).abs() <= 136 * 2.0 ** -24 * mag).all())
+
+
+# One token's products of 2^26 and ones from all others, in every element of G: the large term's chain of 64 tokens loses up to
+# 63 of its ones, the others are integers below 2^24, and G is rounded once to multiples of 8. A single chain loses them all.
+@pytest.mark.parametrize("M,N,K,first", [(4096, 64, 64, 0), (4096, 130, 80, 2000), (4129, 65, 96, 33), (190, 64, 64, 130),
+                                         (224, 33, 64, 100)])
+def test_backward_sums_tokens_in_short_chains(F, M, N, K, first):
+    announce(f"f32 backward chains {M}x{N}x{K} large term at {first}")
+    dY, X = torch.ones(M, N, device="cuda"), torch.ones(M, K, device="cuda")
+    dY[first], X[first] = 2.0 ** 13, 2.0 ** 13
+    W = torch.full((N, K), 0.5, device="cuda")
+    s, c, alpha = F.scales_init(W, NV, 8)
+    _, _, G = F.recon_gemm_bwd(dY, X, W, NV, 8, s, c, alpha, want_G=True)
+    assert float((G.double() - (2.0 ** 26 + M - 1)).abs().max()) <= 63 + 4
