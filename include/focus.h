@@ -113,7 +113,9 @@ typedef enum {
 } focus_call;
 
 /* Workspace bytes a call needs for the given sizes (M = tokens, N = rows / out features,
- * K = in features; unused sizes are ignored). Host-only; returns 0 for invalid arguments. */
+ * K = in features; unused sizes are ignored). Host-only; returns 0 for invalid arguments. A size for M
+ * tokens serves every smaller M, except for FOCUS_CALL_RECON_GEMM_BWD: how the backward splits the
+ * token range depends on M, and fewer tokens can take more splits. Ask for each M that is used. */
 size_t focus_workspace_size(int call, const focus_qconfig *q, int64_t M, int64_t N, int64_t K);
 
 /* Absmax initialisation of the learnable scales (Sec. 3.2 "initialized via absmax", Eq. 2-3).

@@ -91,11 +91,8 @@ class BlockCalibrator:
         lr_s, lr_c = LEARNING_RATES[w.fmt]
         self.hyper = hyper or Hyper(lr_s, lr_c)
         q = F.qconfig(w.fmt, self.sb)
-        M = max(w.M, max_tokens or 0)
-        self.ws = F.workspace(max(F.workspace_size(F.CALL_FAKEQUANT_FWD, q),
-                                  max(F.workspace_size(F.CALL_RECON_GEMM_BWD, q, M, l.N, l.K) for l in w.linears),
-                                  max(F.workspace_size(F.CALL_RECON_GEMM_FWD, q, M, l.N, l.K) for l in w.linears)),
-                              device)
+        self.ws = F.workspace(F.workspace_size(F.CALL_FAKEQUANT_FWD, q), device)
+        self.reserve(max(w.M, max_tokens or 0))
         self.layers = {l.name: LayerState(synth.weight(w, l, device=device), w.fmt, self.sb, self.ws)
                        for l in w.linears}
         self.t = 0
@@ -132,6 +129,17 @@ class BlockCalibrator:
                   for l in w.linears}
         return {k: float(v.item()) for k, v in losses.items()}
 
+    def reserve(self, tokens: int) -> None:
+        """Grows the workspace (its domain flag kept) to what a batch of `tokens` needs: the size for more tokens does not
+        always do, since the backward may split fewer tokens into more parts. For use before the first step."""
+        q = F.qconfig(self.w.fmt, self.sb)
+        need = max(F.workspace_size(call, q, tokens, l.N, l.K) for l in self.w.linears
+                   for call in (F.CALL_RECON_GEMM_BWD, F.CALL_RECON_GEMM_FWD))
+        if self.ws.numel() < need:
+            ws = F.workspace(need, self.device)
+            ws[:256] = self.ws[:256]
+            self.ws = ws
+
     def check_domain(self) -> None:
         st = F.check_flags(self.ws)
         if st != F.OK:
@@ -144,6 +152,7 @@ def calibrate(w: synth.Workload, variant: str, steps: int = EPOCH_STEPS, M: int 
     M = M or w.M
     eval_M = eval_M or M
     cal = BlockCalibrator(w, variant, hyper, device, max_tokens=max(M, eval_M))
+    cal.reserve(M)
     before = cal.run_batch(EVAL_STEP, eval_M, learn=False)
     curve = []
     torch.cuda.synchronize()

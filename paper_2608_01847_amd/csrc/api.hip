@@ -67,12 +67,22 @@ focus_status hip_status(hipError_t e) { return e == hipSuccess ? FOCUS_OK : FOCU
 
 size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
-size_t dx_ws(int64_t M, int64_t N, int64_t K) {
-    return std::max(plan_dx(kF32, M, N, K).ws_bytes, plan_dx(kBF16, M, N, K).ws_bytes);
+// The sizes of the forward and of the input gradient do not fall as M grows (a workspace for the largest batch serves
+// every smaller one), though their plans take smaller tiles and more splits for fewer tokens.
+
+// Column sums of every tile row and of the whole: rows of 64 at most, or of 32 where fp32 outputs have fewer than 256
+// tiles of 64 x 64, whose sums are fewer than 2 x 256 x 64.
+size_t fwd_ws(int64_t M, int64_t N) {
+    const int64_t rows64 = (M + 63) / 64 * N, rows32 = std::min<int64_t>((M + 31) / 32 * N, 2 * kMfmaConcurrentWgs * kF32Tile);
+    return kWsHeader + (size_t)(std::max(rows64, rows32) + N) * sizeof(double);
 }
 
-size_t fwd_ws(int64_t M, int64_t N, int64_t K) {
-    return std::max(plan_fwd(kF32, M, N, K).ws_bytes, plan_fwd(kBF16, M, N, K).ws_bytes);
+// fp32: the transposed W_hat and the forward's sums; bf16: the splits' sums, as many as any M up to this one takes
+size_t dx_ws(int64_t M, int64_t N, int64_t K) {
+    const size_t transposed = kWsHeader + round256((size_t)N * (size_t)K * sizeof(float)) + fwd_ws(M, K);
+    const int64_t splits = dx_max_splits(N), mk = M * K;
+    const int64_t sums = splits > 1 ? (mk > kDxSums / splits ? kDxSums : splits * mk) : 0;
+    return std::max(transposed, kWsHeader + (size_t)sums * sizeof(float));
 }
 
 size_t bwd_ws(int fmt, int sb, int64_t M, int64_t N, int64_t K) {
@@ -171,7 +181,7 @@ size_t focus_workspace_size(int call, const focus_qconfig *q, int64_t M, int64_t
             return kWsHeader;
         case FOCUS_CALL_RECON_GEMM_FWD:
             if (M < 0 || N < 0 || K < 0 || M > kMaxDim || N > kMaxDim || K > kMaxDim) return 0;
-            return fwd_ws(M, N, K);
+            return fwd_ws(M, N);
         case FOCUS_CALL_RECON_GEMM_BWD:
             if (check_rows_k(N, K, B) != FOCUS_OK || M < 0 || M > kMaxDim) return 0;
             return bwd_ws(q->format, q->sub_block, M, N, K);
@@ -247,7 +257,7 @@ focus_status focus_recon_gemm_fwd(const void *X_hat, const void *W_hat, int op_d
     if ((M > 0 && K > kMaxElems / M) || (N > 0 && K > kMaxElems / N) || (M > 0 && N > kMaxElems / M))
         return FOCUS_ERR_SHAPE;
     if (!all_aligned({X_hat, W_hat, Y_ref, dY})) return FOCUS_ERR_SHAPE;
-    FOCUS_TRY(check_ws(ws, ws_bytes, fwd_ws(M, N, K)));
+    FOCUS_TRY(check_ws(ws, ws_bytes, fwd_ws(M, N)));
     if (M == 0 || N == 0) return FOCUS_OK;
     const FwdPlan p = plan_fwd(op_dtype, M, N, K);
     return hip_status(launch_recon_fwd(p, op_dtype, X_hat, W_hat, M, N, K, Y_ref, dY, loss_out, col_sq_opt, ws,
@@ -259,7 +269,7 @@ focus_status focus_recon_gemm_fwd_mxfp4(const uint8_t *X_codes, const uint8_t *X
                                         const void *Y_ref, void *dY, double *loss_out, double *col_sq_opt,
                                         void *ws, size_t ws_bytes, focus_stream stream) {
     FOCUS_TRY(check_fwd_mx_args(X_codes, X_scales, W_codes, W_scales, M, N, K, Y_ref, dY, loss_out));
-    FOCUS_TRY(check_ws(ws, ws_bytes, fwd_ws(M, N, K)));
+    FOCUS_TRY(check_ws(ws, ws_bytes, fwd_ws(M, N)));
     if (M == 0 || N == 0) return FOCUS_OK;
     if (!mfma_fwd_mx_supported(M, N, K)) return FOCUS_ERR_SHAPE;
     return hip_status(launch_recon_fwd_mx(X_codes, X_scales, W_codes, W_scales, M, N, K, Y_ref, dY, loss_out,

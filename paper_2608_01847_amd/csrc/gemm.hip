@@ -397,6 +397,9 @@ hipError_t launch_recon_fwd(const FwdPlan &p, int op_dt, const void *X, const vo
     return launch_fwd_finish(p.mtiles, M, N, colpart, col_sq, loss_out, st);
 }
 
+// a split of the input gradient keeps >= 8 steps of 32 n
+int64_t dx_max_splits(int64_t N) { return std::max<int64_t>(1, std::min<int64_t>(cdiv(N, 32) / 8, 64)); }
+
 DxPlan plan_dx(int op_dt, int64_t M, int64_t N, int64_t K) {
     DxPlan p{0, 1, N, 0};
     if (op_dt != kBF16 || !mfma_dx_supported(M, N, K)) {  // (M and K are positive past this)
@@ -406,13 +409,13 @@ DxPlan plan_dx(int op_dt, int64_t M, int64_t N, int64_t K) {
     p.path = 1;
     // Few output tiles leave CUs idle, so the n range is split to fill the chip in whole rounds: minimise
     // rounds * (32-n steps per split + 8 for the tile's end) plus the traffic of the splits' fp32 sums, written and
-    // read once (about 4 MB in the time of a step), each split keeping >= 8 steps; at most 256 MB of sums, and
-    // none where the tiles already make four rounds.
+    // read once (about 4 MB in the time of a step); at most kDxSums, and none where the tiles already make four rounds.
+    // (A quarter of kDxSums, one round of tiles, took up to a quarter longer by this measure: 5,779 x 13,728 x 1,344.)
     const int64_t tiles = cdiv(M, kMfmaTileM) * cdiv(K, kMfmaTileK), steps = cdiv(std::max<int64_t>(N, 1), 32);
     int64_t best = -1;
     const int64_t most = tiles >= 4 * kMfmaConcurrentWgs
                              ? 1
-                             : std::min<int64_t>(std::min<int64_t>(steps / 8, 64), (int64_t(1) << 26) / (M * K));
+                             : std::min<int64_t>(dx_max_splits(N), kDxSums / (M * K));
     for (int64_t s = 1; s <= std::max<int64_t>(1, most); s++) {
         const int64_t cost = cdiv(tiles * s, kMfmaConcurrentWgs) * (cdiv(steps, s) + 8) +
                              (s > 1 ? s * M * K * 8 / 4000000 + 4 : 0);

@@ -65,6 +65,8 @@ struct DxPlan {
     size_t ws_bytes;
 };
 
+constexpr int64_t kDxSums = int64_t(1) << 26;  // fp32 sums of a split input gradient (256 MB)
+int64_t dx_max_splits(int64_t N);              // for any M and K
 DxPlan plan_dx(int op_dt, int64_t M, int64_t N, int64_t K);
 hipError_t launch_recon_dx(const DxPlan &p, int op_dt, const void *dY, const void *W_hat, int64_t M, int64_t N, int64_t K,
                            void *dX, void *ws, hipStream_t st);

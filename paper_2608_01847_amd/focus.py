@@ -374,8 +374,9 @@ def recon_gemm_dx(dY: torch.Tensor, W_hat: torch.Tensor, ws=None, out=None) -> t
     assert W_hat.shape[0] == N and W_hat.dtype == dY.dtype
     dX = out if out is not None else torch.empty(M, K, dtype=dY.dtype, device=dY.device)
     need = workspace_size(CALL_RECON_GEMM_DX, qconfig(MXFP4, 8), M, N, K)
-    if ws is None or ws.numel() < need:
-        ws = workspace(need, dY.device)
+    if ws is None or ws.numel() < need:  # up to 256 MB; only the header's domain flag has to be zero
+        ws = torch.empty(need, dtype=torch.uint8, device=dY.device)
+        ws[:256].zero_()
     _check(lib().focus_recon_gemm_dx(_ptr(dY), _ptr(W_hat), _dt(dY), M, N, K, _ptr(dX), _ptr(ws), ws.numel(),
                                      _stream()), "focus_recon_gemm_dx")
     return dX

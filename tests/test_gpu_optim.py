@@ -205,3 +205,17 @@ def test_epoch_on_correlated_inputs_lowers_the_loss(F):
         assert rel[v] < 1.0, (v, res[v]["rel_to_rtn"])
         assert res[v]["train_curve"][-1] < res[v]["train_curve"][0], (v, res[v]["train_curve"])
     assert rel["crs_dgs"] < rel["scale"], rel
+
+
+def test_calibration_allocates_its_workspace_before_the_first_step(F, monkeypatch):
+    """Training on fewer tokens than the held-out batch has, at sizes where the backward's workspace is larger for the
+    fewer: every step runs in the calibrator's own workspace, whose domain flag check_domain reads."""
+    from paper_2608_01847_amd import calib, synth
+    w = synth.Workload(name="short", fmt=0, sub_block=8, M=1536, linears=(synth.Linear("a", 128, 256, "x"),), inputs={"x": 256})
+    size = lambda M: F.workspace_size(F.CALL_RECON_GEMM_BWD, F.qconfig(0, 8), M, 128, 256)
+    assert size(1024) > max(size(1536), F.workspace_size(F.CALL_RECON_GEMM_FWD, F.qconfig(0, 8), 1536, 128, 256))
+    announce("calibration 8 steps of 1024 tokens, held-out 1536")
+    made, make = [], F.workspace
+    monkeypatch.setattr(F, "workspace", lambda *a, **k: made.append(a) or make(*a, **k))
+    calib.calibrate(w, "crs", steps=8, M=1024, eval_M=1536)
+    assert len(made) <= 3
