@@ -291,7 +291,8 @@ kl_top_kernel(const void *__restrict__ Zs, const void *__restrict__ Zt, int64_t 
 #pragma unroll
             for (int u = 0; u < kSample / 256; u++) fn(sk[u]);
         }, 0u, 0, rem_s);
-        // the bound as a value: an element's key is at or above `lower` when the element is at or above it
+        // the bound as a value: an element whose key is at or above `lower` is not below it. (Not "at or above it": a
+        // NaN's key is above all others, or below them with its sign set, and the select below is by key.)
         const float lowf = __uint_as_float(((lower & 0x80000000u) ? lower ^ 0x80000000u : ~lower) &
                                            (IN == kBF16 ? 0xFFFF0000u : 0xFFFFFFFFu));
         // ---- one pass over both rows: the elements at or above the bound into this wave's list ----
@@ -323,7 +324,7 @@ kl_top_kernel(const void *__restrict__ Zs, const void *__restrict__ Zt, int64_t 
             if (valid) a = reinterpret_cast<const elem_t *>(zt)[i], b = reinterpret_cast<const elem_t *>(zs)[i];
             const float av = value(a, 0), bv = value(b, 0);
             bad = bad || (valid && (!(__builtin_fabsf(av) < INFINITY) || !(__builtin_fabsf(bv) < INFINITY)));
-            const bool cand = valid && av >= lowf;
+            const bool cand = valid && !(av < lowf);
             const uint64_t m = __ballot(cand);
             if (cand) put(wn + (uint32_t)__popcll(m & below), i, a, b);
             wn += (uint32_t)__popcll(m);
@@ -336,11 +337,11 @@ kl_top_kernel(const void *__restrict__ Zs, const void *__restrict__ Zt, int64_t 
                 if constexpr (IN == kBF16) {
                     // bit 15 of a half: its exponent is all ones (no carry crosses the halves)
                     inf |= ((a[q] & 0x7FFF7FFFu) + 0x00800080u) | ((b[q] & 0x7FFF7FFFu) + 0x00800080u);
-                    mask |= (value(a[q], 0) >= lowf ? 1u : 0u) << (2 * q);
-                    mask |= (value(a[q], 1) >= lowf ? 1u : 0u) << (2 * q + 1);
+                    mask |= (value(a[q], 0) < lowf ? 0u : 1u) << (2 * q);
+                    mask |= (value(a[q], 1) < lowf ? 0u : 1u) << (2 * q + 1);
                 } else {
                     inf |= ((a[q] & 0x7FFFFFFFu) + 0x00800000u) | ((b[q] & 0x7FFFFFFFu) + 0x00800000u);
-                    mask |= (value(a[q], 0) >= lowf ? 1u : 0u) << q;
+                    mask |= (value(a[q], 0) < lowf ? 0u : 1u) << q;
                 }
             }
             bad = bad || (valid && (inf & 0x80008000u & (IN == kBF16 ? ~0u : 0x80000000u)));

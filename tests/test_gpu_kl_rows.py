@@ -73,3 +73,23 @@ def test_values_that_are_not_finite_raise_the_flag(F, V, dt, which, at, value):
     (zs if which == "s" else zt)[1, at] = value
     F.kl_top(zs.cuda(), zt.cuda(), 50, ws=ws)
     assert F.check_flags(ws) == F.ERR_DOMAIN
+
+
+# A teacher's NaN has the highest key and is selected (with its sign set, the lowest, and is not), whichever way its row takes;
+# rows beside it keep their results.
+@pytest.mark.parametrize("V", [1000, 8001, 32000])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("at", [0, 501, 999])
+def test_a_teacher_nan_shows_in_the_loss(F, V, dt, at):
+    announce(f"kl_top teacher NaN V={V} {dt} at {at}")
+    g = torch.Generator().manual_seed(V + at)
+    zs, zt = torch.randn(3, V, generator=g).to(dt).cuda(), torch.randn(3, V, generator=g).to(dt).cuda()
+    clean, _ = F.kl_top(zs, zt, 50)
+    zt[1, at] = float("nan")
+    dZ, loss = F.kl_top(zs, zt, 50)
+    assert bool(torch.isnan(loss)) and bool(torch.isnan(dZ[1, at]))
+    assert torch.equal(dZ[0], clean[0]) and torch.equal(dZ[2], clean[2])
+    bits = torch.int16 if dt == torch.bfloat16 else torch.int32
+    zt.view(bits)[1, at] |= -(1 << 15) if dt == torch.bfloat16 else -(1 << 31)
+    dZ, loss = F.kl_top(zs, zt, 50)
+    assert not bool(torch.isnan(loss)) and dZ[1, at].item() == 0.0
