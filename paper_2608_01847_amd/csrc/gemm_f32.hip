@@ -384,16 +384,20 @@ bwd_f32_kernel(const float *__restrict__ dY, const float *__restrict__ X, int64_
 
 }  // namespace
 
-// Buffer offsets are 32-bit: a tile's rows must span less than 2^31 bytes.
+// Buffer offsets are 32-bit: a tile's rows must span less than 2^31 bytes. The tiles make a one-dimensional grid, whose
+// work-items (256 per tile) must stay below 2^32.
+static bool f32_grid_fits(int64_t rows, int64_t cols) {
+    return ((rows + kF32Tile - 1) / kF32Tile) * ((cols + kF32Tile - 1) / kF32Tile) < (int64_t(1) << 24);
+}
+
 bool f32_fwd_supported(int64_t M, int64_t N, int64_t K) {
-    return K % 16 == 0 && int64_t(kF32Tile) * K * 4 < (int64_t(1) << 31) &&
-           ((M + 31) / 32) * ((N + 31) / 32) < (int64_t(1) << 31);
+    return K % 16 == 0 && int64_t(kF32Tile) * K * 4 < (int64_t(1) << 31) && f32_grid_fits(M, N);
 }
 
 bool f32_bwd_supported(int64_t M, int64_t N, int64_t K) {
     (void)M;
     return int64_t(kF32TokenStep) * N * 4 < (int64_t(1) << 31) && int64_t(kF32TokenStep) * K * 4 < (int64_t(1) << 31) &&
-           ((N + kF32Tile - 1) / kF32Tile) * ((K + kF32Tile - 1) / kF32Tile) < (int64_t(1) << 31);
+           f32_grid_fits(N, K);
 }
 
 hipError_t launch_fwd_f32(int tile, const float *X, const float *W, int64_t M, int64_t N, int64_t K, const float *Yref,

@@ -73,3 +73,11 @@ def test_input_gradient_splits_that_few_tiles_need():
     assert plan_dx(BF16, 4096, 32000, 2560).splits == 3
     assert plan_dx(BF16, 640, 31808, 1184).splits > 8
     assert plan_dx(BF16, 65536, 9728, 2560).splits == 1
+
+
+def test_fp32_outputs_past_one_grid_take_the_two_dimensional_one():
+    """2^24 tiles of 256 threads are 2^32 work-items, more than one launch dimension holds."""
+    assert plan_fwd(F32, 1 << 21, (1 << 15) - 64, 16).path == 2
+    assert plan_fwd(F32, 1 << 21, 1 << 15, 16).path == 0
+    assert plan_bwd(F32, MX, 8, 1, 1 << 20, (1 << 16) - 64).path == 2
+    assert plan_bwd(F32, MX, 8, 1, 1 << 20, 1 << 16).path == 0
