@@ -91,3 +91,30 @@ def test_backward_sums_tokens_in_short_chains(F, M, N, K, first):
     s, c, alpha = F.scales_init(W, NV, 8)
     _, _, G = F.recon_gemm_bwd(dY, X, W, NV, 8, s, c, alpha, want_G=True)
     assert float((G.double() - (2.0 ** 26 + M - 1)).abs().max()) <= 63 + 4
+
+
+# Rows whose tiles pass 2^31 bytes take the kernels without buffer offsets. Operands of -1, 0 and 1: the partial sums stay far
+# below 2^24.
+def test_rows_past_the_buffer_range(F):
+    from host_plans import plan_bwd, plan_fwd
+    M, N, K = 2, 3, (1 << 23) + 16
+    assert plan_fwd(F.F32, M, N, K).path == 0 and plan_bwd(F.F32, NV, 16, M, 1, 2 * K).path == 0
+    announce(f"f32 forward {M}x{N}x{K}, backward {M}x1x{2 * K}")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    def unit(*shape):
+        return torch.randint(-1, 2, shape, generator=g, device="cuda").float()
+    X, W, Y = unit(M, K), unit(N, K), unit(M, N)
+    dY, loss, _ = F.recon_gemm_fwd(X, W, Y)
+    D = (X.double() @ W.double().t()) - Y.double()
+    scale = torch.tensor(2.0 / (M * N), dtype=torch.float64).float().cuda()
+    assert torch.equal(dY, D.float() * scale) and abs(loss.item() - float((D * D).sum()) / (M * N)) <= 4e-15 * loss.item()
+    K *= 2
+    dY, X, W = unit(M, 1), unit(M, K), torch.randn(1, K, generator=g, device="cuda") * 0.02
+    s, c, alpha = F.scales_init(W, NV, 16)
+    gs, gc, _ = F.recon_gemm_bwd(dY, X, W, NV, 16, s, c, alpha)
+    G = (dY.t() @ X).contiguous()
+    rs, rc = F.fakequant_bwd(G, W, NV, 16, s, c, alpha)
+    mag = (G.abs().view(-1, 16) * 12.0).sum(1) * float(alpha)  # |q - m u| <= 12; 16 terms in either order and a product
+    assert bool(((gs - rs).abs().view(-1) <= 34 * 2.0 ** -24 * mag).all())
+    mag = (G.abs() * W.abs()).view(-1, 16).sum(1)
+    assert bool(((gc - rc).abs().view(-1) <= 36 * 2.0 ** -24 * mag).all())
