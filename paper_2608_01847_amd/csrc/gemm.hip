@@ -290,7 +290,7 @@ static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // Rows of a bf16 / MXFP4 forward tile: 128 x 128 tiles while they are at most two (MXFP4) or one and a half (bf16)
 // per CU, else 256 x 256. With 264 small tiles (3,000 x 1,368 x 2,176) they took 22.3 and 40.6 us for 32.5 and 55.9,
 // with 512 (2,048 x 4,096 x 4,096) 36.8 and 109 for 43.6 and 99, with 960 40 and 85 for 33 and 61.
-static int64_t fwd_tile_rows(int64_t M, int64_t N, bool mx) {
+int64_t fwd_tile_rows(int64_t M, int64_t N, bool mx) {
     return cdiv(M, kSmallTile) * cdiv(N, kSmallTile) <= (mx ? 2 * kMfmaConcurrentWgs : 3 * kMfmaConcurrentWgs / 2)
                ? kSmallTile : kMfmaTileM;
 }

@@ -29,6 +29,10 @@ def plan_fwd(op_dt, M, N, K):
     return _planner("_ZN5focus8plan_fwdEilll", FwdPlan, [i32, i64, i64, i64])(op_dt, M, N, K)
 
 
+def fwd_tile_rows(M, N, mx):
+    return _planner("_ZN5focus13fwd_tile_rowsEllb", i64, [i64, i64, ctypes.c_bool])(M, N, mx)
+
+
 def plan_bwd(op_dt, fmt, sb, M, N, K, want_G=False):
     return _planner("_ZN5focus8plan_bwdEiiilllb", BwdPlan, [i32, i32, i32, i64, i64, i64, ctypes.c_bool])(
         op_dt, fmt, sb, M, N, K, want_G)

@@ -29,8 +29,8 @@ def operand(g, rows, K):
     return code[:, 0::2] | (code[:, 1::2] << 4), GRID[i] * (1.0 - 2.0 * s)
 
 
-# M x N in 128 x 128 tiles: the sixth and seventh shapes lie on either side of the rule's line (384 tiles for bf16, 512 for
-# MXFP4), 16 x 24 = 384 and 16 x 25 = 400
+# M x N in 128 x 128 tiles: the sixth and seventh shapes lie on either side of bf16's line of 384 tiles, 16 x 24 = 384 and
+# 16 x 25 = 400 (MXFP4's line of 512: test_gpu_large_tiles.py)
 @pytest.mark.parametrize("M,N,K", [(4, 8, 128), (124, 136, 256), (128, 128, 384), (260, 120, 640), (1000, 264, 1152),
                                    (2048, 3072, 128), (2048, 3080, 128), (4, 1024, 128), (508, 1032, 128)])
 def test_small_tiles_are_exact(F, M, N, K):

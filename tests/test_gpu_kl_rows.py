@@ -40,6 +40,9 @@ def at_offset(x, off):
     (3, 12290, 500, torch.float32, (1, 2, 3), False), (2, 4096, 100, torch.bfloat16, (0, 0, 0), True),
     (2, 4095, 100, torch.bfloat16, (5, 5, 5), False), (2, 4103, 50, torch.float32, (0, 0, 1), False),
     (2, 4110, 1, torch.bfloat16, (0, 7, 0), False), (2, 65537, 1400, torch.bfloat16, (0, 0, 0), False),
+    # the largest k that the sample takes at this length, and the passes past it
+    (2, 32000, 1583, torch.bfloat16, (0, 0, 0), False), (2, 32000, 1584, torch.float32, (1, 0, 0), True),
+    (2, 32000, 4000, torch.bfloat16, (0, 0, 0), True),
 ])
 def test_rows_of_any_alignment(F, C, T, V, k, dt, offs, ties):
     announce(f"kl_top rows T={T} V={V} k={k} {dt} offsets={offs} ties={ties}")

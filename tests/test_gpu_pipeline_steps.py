@@ -1,14 +1,12 @@
-"""GPU parity of the reconstruction GEMMs' main loops at every step count their schedules tell apart.
+"""GPU parity of the reconstruction GEMMs' main loops over short reductions.
 
-Both GEMMs read each half-step's operand fragments one step ahead, into three register sets that
-rotate with a period of three steps. Their loops therefore run whole groups of three steps plus a
-remainder of zero, one or two, and the forward renames its sets once before the steps that bring in
-the Y_ref tile. These cases check each such count against the oracle:
+These sizes take the 128 x 128-tile kernels, whose loops run one step at a time over a ring of four stages. The 256 x
+256-tile kernels, whose register sets rotate with a period of three steps, are covered at every remainder by
+test_gpu_large_tiles.py. Each count against the oracle:
   * forward, FP4 operands and the bf16-operand forward through the same check: K in {512, 640, 768,
-    1152} gives the FP4 kernel 1, 2, 3 and 6 operand steps before its Y_ref steps, and the bf16 kernel
-    12, 16, 20 and 32;
-  * forward, bf16 operands alone: K in {96, 128, 160, 192, 224} runs 3 to 7 steps, which is fewer
-    than, as many as, and just more than its Y_ref steps;
+    1152} runs 4 to 9 steps of 128, and 16 to 36 of 32 for bf16;
+  * forward, bf16 operands alone: K in {96, 128, 160, 192, 224} runs 3 to 7 steps, as many as the ring has stages,
+    fewer and more;
   * backward, packed MXFP4 and bf16 operands, compared bit for bit with each other and against the
     oracle: a 4096 x 4096 layer fills the chip with one token split, so M in {32, 64, 96, 128, 160, 224}
     tokens runs 1 to 7 steps of 32 tokens in every workgroup.

@@ -5,7 +5,7 @@ and 3). The backward rebuilds the bf16 operand from the codes and scale bytes th
 fake quantisation returns, so checked here:
   * bit-identical gradients to the backward on the bf16 X_hat (same operand values, same tiles,
     splits and accumulation order), on ragged shapes (token counts off the 32-token step and the
-    split length, K off the 256 tile, one 32-wide block, N off the tile), every sub-block size and
+    split length, K off the tile, one 32-wide block, N off the tile), every sub-block size and
     the baseline without coefficients, at the initial and a perturbed parameter state;
   * against the oracle (its own fake quantisation, fp64 products): grad_s, grad_c within 2e-2, the
     bf16 GEMM tolerance;

@@ -5,7 +5,7 @@ Eq. 1 and 3), so the forward can run on the block-scaled FP4 MFMA from the codes
 that the library's fake quantisation returns. Checked here:
   * against the oracle (its own fake quantisation, fp64 products): loss, column sums of D^2 and
     dY within 2e-2 (the bf16 GEMM tolerance; dY is bf16), on ragged shapes (token counts and
-    output features off the 256 tile, one and several 128-wide K steps) and a hidden-2560 decoder
+    output features off the tile, one and several 128-wide K steps) and a hidden-2560 decoder
     block narrowed 4x, at the initial and a perturbed parameter state;
   * against the bf16 forward on the same operands: the two compute the same sums and differ only
     in the fp32 accumulation order (1e-4 on the loss and column sums);
