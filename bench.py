@@ -9,6 +9,7 @@ seeded synthetic tensors resident in HBM before timing starts. Prints one JSON l
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME] [--no-cpu-baseline]
 """
 import argparse
+import ctypes
 import hashlib
 import json
 import os
@@ -23,7 +24,7 @@ DEFAULT_WORKLOAD = "block8192_mxfp4"
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 PEAK_FP4_TFLOPS = 10100.0   # MI355X dense MXFP4 MFMA
 PEAK_HBM_GBPS = 8000.0      # MI355X HBM3E
-PEAK_FP32_TFLOPS = 157.3    # MI355X fp32 vector (the fp32 operand path runs on VALU FMAs)
+PEAK_FP32_TFLOPS = 157.3    # MI355X dense fp32 MFMA (the fp32 operand path)
 
 
 def parse():
@@ -130,6 +131,29 @@ def traffic_from_profile(kernel: str, src_hash: str, path):
     if not entry or entry.get("source_hash") != src_hash:
         return None
     return entry.get("bytes_per_launch")
+
+
+def gemm_kernel(lib, call: str, w, sb: int, mx_fwd: bool) -> str:
+    """The kernel that the library launches for a reconstruction GEMM of the workload's linear with the most products
+    (its tile is the library's own plan, asked by the planners' linker names)."""
+    class BwdPlan(ctypes.Structure):
+        _fields_ = [("path", ctypes.c_int), ("tile", ctypes.c_int), ("splits", ctypes.c_int64), ("chunk", ctypes.c_int64),
+                    ("ws_bytes", ctypes.c_size_t)]
+    i32, i64 = ctypes.c_int, ctypes.c_int64
+    lin = max(w.linears, key=lambda l: l.N * l.K)
+    if w.dtype == "f32":
+        return {"recon_gemm_fwd": "fwd_f32_kernel", "recon_gemm_bwd": "bwd_f32_kernel"}[call]
+    if call == "recon_gemm_fwd":
+        rows = getattr(lib, "_ZN5focus13fwd_tile_rowsEllb")
+        rows.restype, rows.argtypes = i64, [i64, i64, ctypes.c_bool]
+        if rows(w.M, lin.N, mx_fwd) == 128:
+            return "fwd_small_kernel"
+        return "fwd_mfma_kernel_mx" if mx_fwd else "fwd_mfma_kernel"
+    plan = getattr(lib, "_ZN5focus8plan_bwdEiiilllb")
+    plan.restype, plan.argtypes = BwdPlan, [i32, i32, i32, i64, i64, i64, ctypes.c_bool]
+    if plan(1, w.fmt, sb, w.M, lin.N, lin.K, False).tile == 128:
+        return "bwd_small_kernel"
+    return "bwd_mfma_mx_kernel" if mx_fwd else "bwd_mfma_kernel"
 
 
 def main():
@@ -382,7 +406,7 @@ def main():
     fq_cold_ms = kern_cold["fakequant_act"]["total_ms"] + kern_cold["fakequant_weight"]["total_ms"]
     fq_cold_bytes = kern_cold["fakequant_act"]["units"] * act_b + kern_cold["fakequant_weight"]["units"] * wt_b
 
-    if esz == 4:  # fp32 operands: the VALU kernels
+    if esz == 4:
         peaks = {"recon_gemm_fwd": PEAK_FP32_TFLOPS, "recon_gemm_bwd": PEAK_FP32_TFLOPS}
     else:
         peaks = {"recon_gemm_fwd": PEAK_FP4_TFLOPS if mx_fwd else PEAK_BF16_TFLOPS, "recon_gemm_bwd": PEAK_BF16_TFLOPS}
@@ -394,12 +418,8 @@ def main():
     per_launch_flops = d["units"] / d["launches"]
     achieved = per_launch_flops / (d["avg_ms"] * 1e-3) / 1e12
     src_hash = kernel_source_hash()
-    if esz == 4:
-        kname = {"recon_gemm_fwd": "fwd_f32_kernel", "recon_gemm_bwd": "bwd_f32_kernel"}[dominant]
-    else:
-        kname = {"recon_gemm_fwd": "fwd_mfma_kernel_mx" if mx_fwd else "fwd_mfma_kernel",
-                 "recon_gemm_bwd": "bwd_mfma_mx_kernel" if mx_fwd else "bwd_mfma_kernel"}[dominant]
-    roofline = {"bound": "alu" if esz == 4 else "mfma", "achieved": round(achieved, 2), "peak": peaks[dominant],
+    kname = gemm_kernel(F.lib(), dominant, w, sb, mx_fwd)
+    roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peaks[dominant],
                 "unit": "TFLOP/s", "frac": round(achieved / peaks[dominant], 4),
                 "traffic": traffic_from_profile(kname, src_hash, traffic_path(w.name)),
                 "kernel": kname, "avg_launch_ms": round(d["avg_ms"], 4), "launches": d["launches"],

@@ -34,6 +34,21 @@ def test_algorithmic_bytes_per_tensor():
     assert bench.algorithmic_bytes("absmax_partial_kernel", M, N, K, sb, fmt=1) == w_bf16
 
 
+def test_roofline_names_the_launched_kernel():
+    from paper_2608_01847_amd import focus, synth
+    lib = focus.lib()
+    large = synth.WORKLOADS["block8192_mxfp4"]
+    assert bench.gemm_kernel(lib, "recon_gemm_fwd", large, 8, True) == "fwd_mfma_kernel_mx"
+    assert bench.gemm_kernel(lib, "recon_gemm_bwd", large, 8, True) == "bwd_mfma_mx_kernel"
+    nv = synth.WORKLOADS["block2560_nvfp4"]
+    assert bench.gemm_kernel(lib, "recon_gemm_fwd", nv, 8, False) == "fwd_mfma_kernel"
+    assert bench.gemm_kernel(lib, "recon_gemm_bwd", nv, 8, False) == "bwd_mfma_kernel"
+    few = synth.scaled(synth.WORKLOADS["block2560_mxfp4"], M=256, name="few")
+    assert bench.gemm_kernel(lib, "recon_gemm_fwd", few, 8, True) == "fwd_small_kernel"
+    assert bench.gemm_kernel(lib, "recon_gemm_bwd", few, 8, True) == "bwd_small_kernel"
+    assert bench.gemm_kernel(lib, "recon_gemm_bwd", synth.WORKLOADS["linear256_mxfp4_f32"], 8, False) == "bwd_f32_kernel"
+
+
 def test_step_launch_map():
     from paper_2608_01847_amd import synth
     w = synth.WORKLOADS["block8192_mxfp4"]
