@@ -1,5 +1,5 @@
 // End-to-end chaining of the scale-learning step: the transposed weight operand of dX_hat = dY W_hat
-// and the KL-Top objective on logits (Sec. 4.1: the paper trains end to end with the KL-Top loss,
+// (fp32, and bf16 shapes that dx_mfma_kernel does not take) and the KL-Top objective on logits (Sec. 4.1: the paper trains end to end with the KL-Top loss,
 // k = 1000, following the method it cites for that loss).
 #include <cmath>
 #include <type_traits>
@@ -60,13 +60,6 @@ __device__ __forceinline__ void store_logit(void *p, int64_t i, float v) {
     else reinterpret_cast<float *>(p)[i] = v;
 }
 
-// the same with the non-temporal cache policy (dZ is written once and not read back here)
-template <int IN>
-__device__ __forceinline__ void store_logit_nt(void *p, int64_t i, float v) {
-    if (IN == kBF16) __builtin_nontemporal_store((uint16_t)f32_to_bf16_bits(v), reinterpret_cast<uint16_t *>(p) + i);
-    else __builtin_nontemporal_store(v, reinterpret_cast<float *>(p) + i);
-}
-
 // Logits of elements base + t + 256 u (u = 0 .. kTrips - 1) of a row: a thread's next kTrips elements
 // in its usual order, loaded before any is used so that kTrips loads are in flight at once (the passes
 // are bound by the latency of rows that no longer fit the caches: 16 in flight took the 8192 x 151936
@@ -112,7 +105,8 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *buf) {
 //    softmax statistics and the KL terms then come from LDS, and dZ leaves once, in order: a segment of the
 //    row at a time, zeros with the gathered elements' gradients scattered into them in LDS, as 16-byte stores.
 //    Bound by memory on long rows (two reads of the logits' rows, one write; the sample re-reads up to a
-//    tenth) and by the latency of the LDS phases, which the three rows per CU hide for each other, on short ones.
+//    tenth) and by the latency of the LDS phases, which the rows per CU (bf16 four, fp32 three) hide for each other, on
+//    short ones.
 //    8,192 x 151,936 bf16 logits, k = 1,000: 1.78 ms (4.2 TB/s), where 2-byte loads, zeros stored on the way and
 //    the gathered elements' gradients scattered over them took 2.26; 4,096 x 32,000: 0.21 ms (3.7 TB/s).
 //  * The passes below whenever the gathered set misses the k-th largest key, overflows the lists or
@@ -124,8 +118,8 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *buf) {
 constexpr int kSample = 3072;          // sampled teacher keys (12 per thread)
 constexpr int kCand = 3072;            // gathered elements (LDS lists of 768 per wave)
 constexpr int kPerWave = kCand / 4;
-// Shortest row of the sample: its runs of 8 keys are 10 elements apart or more, and k = 1,000 still passes
-// the rule on r below from V = 4,400 on. (4,096 x 32,000 takes 1.34 ms by the passes, 0.21 by the
+// Shortest row of the sample: its runs of 8 keys are 10 elements apart or more, and k = 1,000 passes
+// the rule on r below from V = 4,472 on. (4,096 x 32,000 takes 1.34 ms by the passes, 0.21 by the
 // sample.)
 constexpr int64_t kSampleMinV = 4096;
 constexpr int kTieMax = 1024;           // ties at the threshold key the gathered path resolves
@@ -667,7 +661,8 @@ kl_top_kernel(const void *__restrict__ Zs, const void *__restrict__ Zt, int64_t 
             float va[kTrips], vb[kTrips];
             load_trips<IN>(zt, base, t, V, va);
             load_trips<IN>(zs, base, t, V, vb);
-            const bool whole = base + 256 * kTrips <= V;  // stores unconditional (see the gather pass)
+            // a whole chunk's stores are unconditional: the compiler then counts the memory operations in flight exactly
+            const bool whole = base + 256 * kTrips <= V;
             for (int u = 0; u < kTrips; u++) {
                 const int64_t i = base + t + 256 * u;
                 if (!whole && i >= V) break;

@@ -21,14 +21,13 @@
 //           column, so the column sums are in-lane plus one cross-lane add.
 // Backward: C = X_hat^T dY (rows = in features k, columns = out features n), i.e. G^T with the
 //           reduction over tokens. Both operands are token-major in memory and are staged as they
-//           lie; transposing LDS reads (ds_read_b64_tr_b16) form the fragments. In the epilogue a
-//           lane holds 4 consecutive k of one n per register group, so a sub-block of 8 is an
-//           in-lane sum of 4 plus one exchange with lane l ^ 32, and a block of 32 is 16 in-lane
-//           values plus the same exchange.
+//           lie; transposing LDS reads (ds_read_b64_tr_b16) form the fragments. The straight-through
+//           epilogue takes G through LDS in row order (ste_epilogue).
+// Input gradient: C = dY W_hat (rows = tokens, columns = in features), dY as the forward's operands, W_hat as the
+//           backward's.
 #include "mfma_common.h"
 
 namespace focus {
-
 
 namespace {
 
@@ -37,8 +36,6 @@ constexpr int kThreads = 256;         // four waves
 constexpr int kLdsBytes = 160 * 1024; // LDS of one gfx950 CU
 
 static_assert(kTile == kMfmaTileM && kTile == kMfmaTileN && kTile == kMfmaTileK, "tile geometry");
-
-
 
 // ---- forward operand staging: direct-to-LDS buffer loads ---------------------------------------
 // The forward operands are K-contiguous, so their tiles go from HBM / L2 straight into LDS with
