@@ -934,7 +934,7 @@ def summarize_counters(fetch_dir, write_dir, workload, out_dir=None):
     print(out)
 
 
-EXTRA_KERNELS = {"transpose_kernel": "transpose_kernel<", "fq_act_bwd_kernel": "fq_act_bwd_kernel<",
+EXTRA_KERNELS = {"transpose_kernel": "transpose_kernel<", "dx_mfma_kernel": "dx_mfma_kernel", "fq_act_bwd_kernel": "fq_act_bwd_kernel<",
                  "kl_top_kernel": "kl_top_kernel<", "adamw_kernel": "adamw_kernel"}
 EXTRAS_CMD = ("rocprofv3 --pmc {c} -d OUT/prof_extras_{d} -o run --output-format csv -- "
               "python3 -u bench.py --steps 1 --warmup 0 --no-cpu-baseline --copy-calibration{wl}")
@@ -942,12 +942,14 @@ EXTRAS_CMD = ("rocprofv3 --pmc {c} -d OUT/prof_extras_{d} -o run --output-format
 
 def extra_launches(kernel, w):
     """One call's launches of a kernel outside the step, in order, with their algorithmic bytes: the
-    transposes of dX (every linear's bf16 W_hat read and written once), the activation straight-through
-    backward (every bf16 block input: X and dX_hat read, dX written), KL-Top (8,192 x 151,936 bf16 logits:
+    transposes of dX (every linear's W_hat read and written once, where the library makes the copy), dX itself in bf16
+    (every linear's dY and W_hat read, dX written), the activation straight-through backward (every bf16 block input: X and dX_hat read, dX written), KL-Top (8,192 x 151,936 bf16 logits:
     both rows read, dZ written) and AdamW (S_fp, then c, of every linear: p, g, m, v read, p, m, v written,
     28 B per fp32 parameter). The bench repeats each call, so a position's launches are pooled."""
     if kernel == "transpose_kernel":
         return [(f"{l.name} {l.N}x{l.K}", 4 * l.N * l.K) for l in w.linears]
+    if kernel == "dx_mfma_kernel":
+        return [(f"{l.name} {l.N}x{l.K}", 2 * (w.M * (l.N + l.K) + l.N * l.K)) for l in w.linears]
     if kernel == "fq_act_bwd_kernel":
         return [(f"{src} {w.M}x{K}", 6 * w.M * K) for src, K in w.inputs.items()]
     if kernel == "kl_top_kernel":

@@ -95,7 +95,7 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *buf) {
 // One workgroup per token row, in one of two ways. Both give the same selected set (the teacher's k
 // largest logits, ties at the k-th value in index order) and the same per-element formulas; the sums
 // run in a fixed order in each, so every result is deterministic.
-//  * Sample-select, when the k largest are a small part of a row: the r-th largest of 3,072 teacher keys,
+//  * Sample-select (SAMPLE), when the k largest are a small part of a row (see kl_sample_rank): the r-th largest of 3,072 teacher keys,
 //    r with a binomial margin of 3 standard deviations over the expected count, lies below the k-th
 //    largest key almost always (10 rows of 8,192 miss at k = 1,000 of 151,936 on independent logits). The
 //    sample is 384 evenly spaced runs of 8 adjacent keys (keys spaced singly touch nearly every memory line
@@ -114,7 +114,9 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *buf) {
 //    the top, LDS histograms); if fewer ties at that key are admitted than exist, the index of the
 //    last admitted tie (256 elements per trip, ballots for the in-trip ranks); online softmax
 //    statistics of both rows over the selected set (per thread, then a fixed tree); KL terms and dZ_s
-//    (zero outside the set).
+//    (zero outside the set). Rows that never take the sample have a kernel without it: as one kernel with it, whose
+//    LDS lets three fp32 rows onto a CU, 1,000 x 60,000 fp32 logits at k = 1,900 took 833 us, now 677 (805 before the
+//    two ways shared their LDS), 4,000 x 12,000 bf16 ones at 2,500 586, now 525.
 constexpr int kSample = 3072;          // sampled teacher keys (12 per thread)
 constexpr int kCand = 3072;            // gathered elements (LDS lists of 768 per wave)
 constexpr int kPerWave = kCand / 4;
@@ -124,19 +126,20 @@ constexpr int kPerWave = kCand / 4;
 constexpr int64_t kSampleMinV = 4096;
 constexpr int kTieMax = 1024;           // ties at the threshold key the gathered path resolves
 constexpr int kSegBytes = 8192;         // dZ segment in LDS (two of them)
-template <int IN>
+template <int IN, bool SAMPLE>
 __global__ void __launch_bounds__(256)
 kl_top_kernel(const void *__restrict__ Zs, const void *__restrict__ Zt, int64_t V, int k, double inv_T,
-              void *__restrict__ dZs, double *__restrict__ row_loss, uint32_t *flag) {
+              void *__restrict__ dZs, double *__restrict__ row_loss, uint32_t *flag, int r) {
     using elem_t = typename std::conditional<IN == kBF16, uint16_t, uint32_t>::type;  // a logit's bits
     constexpr int kEsz = sizeof(elem_t);
     constexpr int E = 16 / kEsz;  // logits per 16 bytes
     // LDS by hand, because rows per CU hide each other's latency (bf16: 34 KB, four rows): the lists' indices and
     // student logits (later gradients) first, then a region that holds the histograms, the lists' teacher
-    // logits and the ties, and after them the two dZ segments. The passes below put their arrays over the lists.
+    // logits and the ties, and after them the two dZ segments. The passes below put their arrays over the lists, or
+    // without the sample into 10 KB of their own (the registers then let four rows onto a CU in fp32 too).
     constexpr int kIdxOff = 0, kBOff = kCand * 4, kRegion = kBOff + kCand * kEsz;
     constexpr int kAOff = kRegion + 3 * 256 * 4, kTieOff = kAOff + kCand * kEsz;
-    constexpr int kLds = std::max(kTieOff + kTieMax * 4, kRegion + 2 * kSegBytes);
+    constexpr int kLds = SAMPLE ? std::max(kTieOff + kTieMax * 4, kRegion + 2 * kSegBytes) : 16;
     __shared__ __attribute__((aligned(16))) char lds[kLds];
     uint32_t *const cand_idx = reinterpret_cast<uint32_t *>(lds + kIdxOff);
     elem_t *const cand_b = reinterpret_cast<elem_t *>(lds + kBOff);
@@ -144,10 +147,14 @@ kl_top_kernel(const void *__restrict__ Zs, const void *__restrict__ Zt, int64_t 
     elem_t *const cand_a = reinterpret_cast<elem_t *>(lds + kAOff);
     uint32_t *const tie_idx = reinterpret_cast<uint32_t *>(lds + kTieOff);
     char *const stage = lds + kRegion;
-    double(*const red_s)[256] = reinterpret_cast<double(*)[256]>(lds);
-    double *const red_d = reinterpret_cast<double *>(lds + 4096);
-    float(*const red_m)[256] = reinterpret_cast<float(*)[256]>(lds + 6144);
-    uint32_t *const scan_buf = reinterpret_cast<uint32_t *>(lds + 8192);
+    __shared__ double own_s[2][256], own_d[256];
+    __shared__ float own_m[2][256];
+    __shared__ uint32_t own_scan[256], own_hist[256];
+    double(*const red_s)[256] = SAMPLE ? reinterpret_cast<double(*)[256]>(lds) : own_s;
+    double *const red_d = SAMPLE ? reinterpret_cast<double *>(lds + 4096) : own_d;
+    float(*const red_m)[256] = SAMPLE ? reinterpret_cast<float(*)[256]>(lds + 6144) : own_m;
+    uint32_t *const scan_buf = SAMPLE ? reinterpret_cast<uint32_t *>(lds + 8192) : own_scan;
+    uint32_t *const hist0 = SAMPLE ? hist[0] : own_hist;
     static_assert(8192 + 1024 <= kRegion, "the passes' arrays lie below the histograms");
     __shared__ uint32_t sel_digit, sel_above;
     __shared__ uint32_t wave_cnt[4], wave_n[4], tie_cnt;
@@ -223,9 +230,7 @@ kl_top_kernel(const void *__restrict__ Zs, const void *__restrict__ Zt, int64_t 
     };
 
     bool done = false;
-    const double kexp = (double)k * kSample / (double)V;  // expected sampled keys at or above the k-th
-    const int r = (int)ceil(kexp) + (int)ceil(3.0 * sqrt(kexp)) + 2;
-    if (!all && V >= kSampleMinV && r <= kSample / 4 && (double)r * (double)V / kSample <= 0.65 * kCand) {
+    if constexpr (SAMPLE) {
         // One histogram pass of a select: counts of add()'s bins (0..255) in one of three histograms, then
         // every wave finds by itself the bin that holds the rem-th largest element (rem becomes its rank within
         // the bin). Histogram p % 3 is cleared again after the next pass's barrier, when every wave has read it,
@@ -574,7 +579,7 @@ kl_top_kernel(const void *__restrict__ Zs, const void *__restrict__ Zt, int64_t 
         if (!all) {
             for (int p = 0; p < kPasses; p++) {
                 const int shift = 24 - 8 * p;
-                hist[0][t] = 0u;
+                hist0[t] = 0u;
                 __syncthreads();
                 for (int64_t base = 0; base < V; base += 256 * kTrips) {
                     float v[kTrips];
@@ -582,12 +587,12 @@ kl_top_kernel(const void *__restrict__ Zs, const void *__restrict__ Zt, int64_t 
     #pragma unroll
                     for (int u = 0; u < kTrips; u++) {
                         const uint32_t key = logit_key<IN>(v[u]);
-                        if (base + t + 256 * u < V && (key & pmask) == prefix) atomicAdd(&hist[0][(key >> shift) & 255u], 1u);
+                        if (base + t + 256 * u < V && (key & pmask) == prefix) atomicAdd(&hist0[(key >> shift) & 255u], 1u);
                     }
                 }
                 __syncthreads();
                 // bins in descending digit order: thread j holds digit 255 - j
-                const uint32_t h = hist[0][255 - t];
+                const uint32_t h = hist0[255 - t];
                 const uint32_t incl = block_scan(h, scan_buf);
                 if (incl - h < remaining && remaining <= incl) {
                     sel_digit = 255u - (uint32_t)t;
@@ -719,11 +724,22 @@ hipError_t launch_transpose(int dt, const void *in, int64_t R, int64_t C, void *
     return hipGetLastError();
 }
 
+// Rank r of the sample's key that bounds the k-th largest logit from below, or 0 where the rows take the passes: the
+// sample's expected count of the k largest with three standard deviations, if the lists hold what lies above it.
+static int kl_sample_rank(int64_t V, int k) {
+    const double kexp = (double)k * kSample / (double)V;
+    const double r = std::ceil(kexp) + std::ceil(3.0 * std::sqrt(kexp)) + 2.0;
+    return (int64_t)k < V && V >= kSampleMinV && r <= kSample / 4 && r * (double)V / kSample <= 0.65 * kCand ? (int)r : 0;
+}
+
 hipError_t launch_kl_top(int dt, const void *Zs, const void *Zt, int64_t T, int64_t V, int k, void *dZs,
                          double *row_loss, double *loss, uint32_t *flag, hipStream_t st) {
     const double inv_T = 1.0 / (double)T;
-    if (dt == kBF16) kl_top_kernel<kBF16><<<(unsigned)T, 256, 0, st>>>(Zs, Zt, V, k, inv_T, dZs, row_loss, flag);
-    else kl_top_kernel<kF32><<<(unsigned)T, 256, 0, st>>>(Zs, Zt, V, k, inv_T, dZs, row_loss, flag);
+    const int r = kl_sample_rank(V, k);
+#define KL(IN, S) kl_top_kernel<IN, S><<<(unsigned)T, 256, 0, st>>>(Zs, Zt, V, k, inv_T, dZs, row_loss, flag, r)
+    if (dt == kBF16) { if (r) KL(kBF16, true); else KL(kBF16, false); }
+    else { if (r) KL(kF32, true); else KL(kF32, false); }
+#undef KL
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     row_mean_kernel<<<1, 256, 0, st>>>(row_loss, T, loss);
