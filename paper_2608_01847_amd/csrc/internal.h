@@ -70,6 +70,7 @@ int64_t dx_max_splits(int64_t N);              // for any M and K
 DxPlan plan_dx(int op_dt, int64_t M, int64_t N, int64_t K);
 hipError_t launch_recon_dx(const DxPlan &p, int op_dt, const void *dY, const void *W_hat, int64_t M, int64_t N, int64_t K,
                            void *dX, void *ws, hipStream_t st);
+bool fwd_finish_in_one(int64_t mtiles, int64_t N);  // column sums and loss by one workgroup
 int64_t fwd_tile_rows(int64_t M, int64_t N, bool mx);  // of a bf16 / packed MXFP4 forward
 FwdPlan plan_fwd(int op_dt, int64_t M, int64_t N, int64_t K);
 BwdPlan plan_bwd(int op_dt, int fmt, int sb, int64_t M, int64_t N, int64_t K, bool want_G);

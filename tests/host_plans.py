@@ -33,6 +33,10 @@ def fwd_tile_rows(M, N, mx):
     return _planner("_ZN5focus13fwd_tile_rowsEllb", i64, [i64, i64, ctypes.c_bool])(M, N, mx)
 
 
+def fwd_finish_in_one(mtiles, N):
+    return _planner("_ZN5focus17fwd_finish_in_oneEll", ctypes.c_bool, [i64, i64])(mtiles, N)
+
+
 def plan_bwd(op_dt, fmt, sb, M, N, K, want_G=False):
     return _planner("_ZN5focus8plan_bwdEiiilllb", BwdPlan, [i32, i32, i32, i64, i64, i64, ctypes.c_bool])(
         op_dt, fmt, sb, M, N, K, want_G)

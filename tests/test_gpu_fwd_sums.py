@@ -8,8 +8,9 @@ from gpu_common import announce, require_gpu
 pytestmark = pytest.mark.gpu
 
 
-# rows of tiles (64 rows each) past one batch of 16 x 8 and inside it, columns past one batch of 256 x 8
-@pytest.mark.parametrize("M,N", [(64 * 131 + 5, 24), (64 * 128, 1032), (64 * 17, 2309), (300, 4097), (1, 2048)])
+# rows of tiles (64 rows each) past one batch of 16 x 8 and inside it, columns past one batch of 256 x 8; 16 rows of tiles (32
+# rows each), the most that one workgroup sums, and 17
+@pytest.mark.parametrize("M,N", [(512, 24), (520, 24), (481, 256), (64 * 131 + 5, 24), (64 * 128, 1032), (64 * 17, 2309), (300, 4097), (1, 2048)])
 def test_sums_are_exact_on_integers(M, N):
     F = require_gpu()
     announce(f"forward sums {M}x{N}")

@@ -1,5 +1,5 @@
 """The 128 x 128-tile forward kernels (bf16 and packed MXFP4) at the edges of their tiles, steps and launch rule,
-and the one-workgroup finishing sums at theirs (up to 4,096 partials and 1,024 columns).
+and the one-workgroup finishing sums at theirs (up to 4,096 partials, 1,024 columns and 16 tile rows).
 
 Operands are FP4 grid values with unit scales, so every product and partial sum is a multiple of 1/4 below 2^22 and
 exact in fp32 in any order: the plain product rounds once to bf16; D = Y_hat - Y_ref is exact, dY one product and one

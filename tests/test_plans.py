@@ -11,7 +11,7 @@ import random
 
 import pytest
 
-from host_plans import plan_bwd, plan_dx, plan_fwd
+from host_plans import fwd_finish_in_one, plan_bwd, plan_dx, plan_fwd
 from paper_2608_01847_amd import focus as F
 
 F32, BF16 = F.F32, F.BF16
@@ -81,3 +81,9 @@ def test_fp32_outputs_past_one_grid_take_the_two_dimensional_one():
     assert plan_fwd(F32, 1 << 21, 1 << 15, 16).path == 0
     assert plan_bwd(F32, MX, 8, 1, 1 << 20, (1 << 16) - 64).path == 2
     assert plan_bwd(F32, MX, 8, 1, 1 << 20, 1 << 16).path == 0
+
+
+def test_many_tile_rows_are_not_summed_by_one_workgroup():
+    """30 us for 102 tile rows of 24 columns, 6 by the two kernels."""
+    assert fwd_finish_in_one(4, 256) and fwd_finish_in_one(16, 256) and fwd_finish_in_one(4, 1024)
+    assert not fwd_finish_in_one(102, 24) and not fwd_finish_in_one(17, 24) and not fwd_finish_in_one(5, 1024)
