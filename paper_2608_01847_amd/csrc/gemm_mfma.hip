@@ -165,20 +165,6 @@ __device__ __forceinline__ void tr_wait15(Frags &f) {
                    "+v"(f.b[2]), "+v"(f.b[3]));
 }
 
-// Position t of a rows x cols tile grid in grouped order: groups of `group` row-tiles (default 4)
-// are walked column by column, so the ~32 workgroups an XCD runs at once cover about 4 x 8 tiles and
-// share 4 row panels and 8 column panels instead of 1 and 32.
-constexpr uint32_t kGroupRows = 4;
-__device__ __forceinline__ void grouped_tile(uint32_t t, uint32_t rows, uint32_t cols, uint32_t &r, uint32_t &c,
-                                             uint32_t group = kGroupRows) {
-    const uint32_t per_group = group * cols;
-    const uint32_t first = (t / per_group) * group;
-    const uint32_t in_group = rows - first < group ? rows - first : group;
-    const uint32_t u = t % per_group;
-    r = first + u % in_group;
-    c = u / in_group;
-}
-
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------

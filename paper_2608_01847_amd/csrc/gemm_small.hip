@@ -55,7 +55,7 @@ template <bool MSE, bool MX>
 __global__ void __launch_bounds__(kThreads, 2)
 fwd_small_kernel(const void *__restrict__ X, const void *__restrict__ W, const uint8_t *__restrict__ Xs,
                  const uint8_t *__restrict__ Ws, int64_t M, int64_t N, int64_t K, const uint16_t *__restrict__ Yref,
-                 uint16_t *__restrict__ dY, float dscale, double *__restrict__ colpart, int tiles_n) {
+                 uint16_t *__restrict__ dY, float dscale, double *__restrict__ colpart, int tiles_n, int group) {
     constexpr int S = 4, kOp = kT * 64, kStage = 2 * kOp + (MX ? 1024 : 0);
     constexpr int kLoads = MX ? 5 : 4;     // loads per slot per thread
     constexpr int kKStep = MX ? 128 : 32;  // k per step
@@ -65,7 +65,9 @@ fwd_small_kernel(const void *__restrict__ X, const void *__restrict__ W, const u
     const int lr = lane & 31, lh = lane >> 5;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const uint32_t tm = tile / (uint32_t)tiles_n, tn = tile % (uint32_t)tiles_n;
+    uint32_t tm, tn;
+    if (group == 1) tm = tile / (uint32_t)tiles_n, tn = tile % (uint32_t)tiles_n;
+    else grouped_tile(tile, gridDim.x / (uint32_t)tiles_n, (uint32_t)tiles_n, tm, tn, (uint32_t)group);
     const int64_t m0 = (int64_t)tm * kT, n0 = (int64_t)tn * kT;
     const int64_t pitch = MX ? K / 2 : K * 2;
     const int64_t nk = (K + kKStep - 1) / kKStep;
@@ -412,12 +414,16 @@ bwd_small_kernel(const uint16_t *__restrict__ dY, const void *__restrict__ X, co
 
 hipError_t launch_fwd_small(const void *X, const void *W, const void *Xs, const void *Ws, int64_t M, int64_t N, int64_t K,
                             const void *Yref, void *dY, float dscale, double *colpart, hipStream_t st) {
-    const int tiles_n = (int)((N + kT - 1) / kT);
-    const dim3 grid((unsigned)((M + kT - 1) / kT) * tiles_n);
+    const int tiles_n = (int)((N + kT - 1) / kT), tiles_m = (int)((M + kT - 1) / kT);
+    const dim3 grid((unsigned)tiles_m * tiles_n);
+    // Where the grid is at least twice as wide as high, groups of up to 8 row tiles are walked column by column, so that
+    // a W panel is read by one XCD for them all; row after row, each row's XCDs read all of W (bf16 512 x 8,320 x 5,504:
+    // 139 us, with 256 x 256 tiles 120, so 106). Narrower grids share enough either way, and square ones lost up to 8%.
+    const int groups = (tiles_m + 7) / 8, group = 2 * tiles_m <= tiles_n ? (tiles_m + groups - 1) / groups : 1;
     const uint8_t *xs = static_cast<const uint8_t *>(Xs), *ws = static_cast<const uint8_t *>(Ws);
     const uint16_t *y = static_cast<const uint16_t *>(Yref);
     uint16_t *d = static_cast<uint16_t *>(dY);
-#define FS(MSE, MX) fwd_small_kernel<MSE, MX><<<grid, kThreads, 0, st>>>(X, W, xs, ws, M, N, K, y, d, dscale, colpart, tiles_n)
+#define FS(MSE, MX) fwd_small_kernel<MSE, MX><<<grid, kThreads, 0, st>>>(X, W, xs, ws, M, N, K, y, d, dscale, colpart, tiles_n, group)
     if (Xs) { if (Yref) FS(true, true); else FS(false, true); }
     else { if (Yref) FS(true, false); else FS(false, false); }
 #undef FS

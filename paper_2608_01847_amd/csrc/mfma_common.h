@@ -1,5 +1,5 @@
-// Pieces shared by the bf16 / MXFP4 MFMA kernels of both tile sizes: operand staging with direct-to-LDS loads
-// and transposing fragment reads.
+// Pieces shared by the bf16 / MXFP4 MFMA kernels of both tile sizes: tile order, operand staging with direct-to-LDS
+// loads, transposing fragment reads and the straight-through epilogue.
 #pragma once
 
 #include "gemm_common.h"
@@ -7,6 +7,20 @@
 namespace focus {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+// Position t of a rows x cols tile grid in grouped order: groups of `group` row-tiles (default 4)
+// are walked column by column, so the ~32 workgroups an XCD runs at once cover about 4 x 8 tiles and
+// share 4 row panels and 8 column panels instead of 1 and 32.
+constexpr uint32_t kGroupRows = 4;
+__device__ __forceinline__ void grouped_tile(uint32_t t, uint32_t rows, uint32_t cols, uint32_t &r, uint32_t &c,
+                                             uint32_t group = kGroupRows) {
+    const uint32_t per_group = group * cols;
+    const uint32_t first = (t / per_group) * group;
+    const uint32_t in_group = rows - first < group ? rows - first : group;
+    const uint32_t u = t % per_group;
+    r = first + u % in_group;
+    c = u / in_group;
+}
 
 // A direct-to-LDS load writes lane L's 16 bytes at LDS byte 16 L from the instruction's base, so
 // each wave fills 1 KB blocks: lane L of block q lands in row 16 q + L / 4, physical chunk L % 4,

@@ -32,7 +32,9 @@ def operand(g, rows, K):
 # M x N in 128 x 128 tiles: the sixth and seventh shapes lie on either side of bf16's line of 384 tiles, 16 x 24 = 384 and
 # 16 x 25 = 400 (MXFP4's line of 512: test_gpu_large_tiles.py)
 @pytest.mark.parametrize("M,N,K", [(4, 8, 128), (124, 136, 256), (128, 128, 384), (260, 120, 640), (1000, 264, 1152),
-                                   (2048, 3072, 128), (2048, 3080, 128), (4, 1024, 128), (508, 1032, 128)])
+                                   (2048, 3072, 128), (2048, 3080, 128), (4, 1024, 128), (508, 1032, 128),
+                                   # tile order: 5 rows of 9 and of 10 columns, 9 of 18 (groups of 5 and 4), 12 of 29
+                                   (516, 1152, 128), (516, 1160, 128), (1036, 2184, 128), (1412, 3680, 256)])
 def test_small_tiles_are_exact(F, M, N, K):
     announce(f"small-tile forward {M}x{N}x{K}")
     g = torch.Generator().manual_seed(M + N + K)
