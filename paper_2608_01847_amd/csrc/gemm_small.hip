@@ -51,7 +51,7 @@ __device__ __forceinline__ void read_step_mx(FwdStepFrags &f, uint32_t a0, uint3
 // ------------------------------------------------------------------------------------------------
 // Forward (see fwd_mfma_kernel): 64 bytes of each operand row per step, four stages of 16 KB (17 KB for MXFP4).
 // 2,048 x 1,024 x 2,560: MXFP4 16.9 us, bf16 34.5 us with the two finishing kernels; on 256 x 256 tiles 29.4 and 62.7.
-template <bool MSE, bool MX>
+template <bool MSE, bool MX, bool WIDE>
 __global__ void __launch_bounds__(kThreads, 2)
 fwd_small_kernel(const void *__restrict__ X, const void *__restrict__ W, const uint8_t *__restrict__ Xs,
                  const uint8_t *__restrict__ Ws, int64_t M, int64_t N, int64_t K, const uint16_t *__restrict__ Yref,
@@ -66,7 +66,7 @@ fwd_small_kernel(const void *__restrict__ X, const void *__restrict__ W, const u
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     uint32_t tm, tn;
-    if (group == 1) tm = tile / (uint32_t)tiles_n, tn = tile % (uint32_t)tiles_n;
+    if constexpr (!WIDE) tm = tile / (uint32_t)tiles_n, tn = tile % (uint32_t)tiles_n;
     else grouped_tile(tile, gridDim.x / (uint32_t)tiles_n, (uint32_t)tiles_n, tm, tn, (uint32_t)group);
     const int64_t m0 = (int64_t)tm * kT, n0 = (int64_t)tn * kT;
     const int64_t pitch = MX ? K / 2 : K * 2;
@@ -419,13 +419,16 @@ hipError_t launch_fwd_small(const void *X, const void *W, const void *Xs, const 
     // Where the grid is at least twice as wide as high, groups of up to 8 row tiles are walked column by column, so that
     // a W panel is read by one XCD for them all; row after row, each row's XCDs read all of W (bf16 512 x 8,320 x 5,504:
     // 139 us, with 256 x 256 tiles 120, so 106). Narrower grids share enough either way, and square ones lost up to 8%.
-    const int groups = (tiles_m + 7) / 8, group = 2 * tiles_m <= tiles_n ? (tiles_m + groups - 1) / groups : 1;
+    const bool wide = 2 * tiles_m <= tiles_n;
+    const int groups = (tiles_m + 7) / 8, group = (tiles_m + groups - 1) / groups;
     const uint8_t *xs = static_cast<const uint8_t *>(Xs), *ws = static_cast<const uint8_t *>(Ws);
     const uint16_t *y = static_cast<const uint16_t *>(Yref);
     uint16_t *d = static_cast<uint16_t *>(dY);
-#define FS(MSE, MX) fwd_small_kernel<MSE, MX><<<grid, kThreads, 0, st>>>(X, W, xs, ws, M, N, K, y, d, dscale, colpart, tiles_n, group)
-    if (Xs) { if (Yref) FS(true, true); else FS(false, true); }
-    else { if (Yref) FS(true, false); else FS(false, false); }
+#define FS(MSE, MX, WIDE) fwd_small_kernel<MSE, MX, WIDE><<<grid, kThreads, 0, st>>>(X, W, xs, ws, M, N, K, y, d, dscale, colpart, tiles_n, group)
+#define FS_W(MSE, MX) if (wide) FS(MSE, MX, true); else FS(MSE, MX, false)
+    if (Xs) { if (Yref) { FS_W(true, true); } else { FS_W(false, true); } }
+    else { if (Yref) { FS_W(true, false); } else { FS_W(false, false); } }
+#undef FS_W
 #undef FS
     return hipGetLastError();
 }
