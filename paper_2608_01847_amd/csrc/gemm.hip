@@ -219,8 +219,8 @@ loss_kernel(const double *__restrict__ col_sq, int64_t N, double inv_mn, double 
 
 // Both of the above in one workgroup, where the partials are few (a launch costs more than their sums): a thread per
 // column, the same order of additions. 4 x 256 partials take 3.9 us,
-// where the two kernels take 4.4 and a launch more; at 16 x 1,024 (7.7) it is no longer ahead. At most 16 tile rows, all
-// loaded at once: with 16 after 16 of them, 32 x 24 partials took 11.8 us and 102 x 24 30, the two kernels 5.9.
+// where the two kernels take 4.4 and a launch more; at 16 x 1,024 (7.7) it is no longer ahead. At most 16 tile rows, one
+// batch of loads: with a second batch behind it, 32 x 24 partials took 11.8 us, and 102 x 24 30, the two kernels 5.9.
 constexpr int kFinishCols = 1024;
 constexpr int64_t kFinishParts = 4096, kFinishRows = 16;
 bool fwd_finish_in_one(int64_t mtiles, int64_t N) {
@@ -232,11 +232,16 @@ fwd_finish_small_kernel(const double *__restrict__ colpart, int64_t mtiles, int6
     __shared__ double cols[kFinishCols];
     __shared__ double part[256];
     for (int64_t n = threadIdx.x; n < N; n += 1024) {
-        double s[kFinishRows];
+        double s[16];
 #pragma unroll
-        for (int g = 0; g < kFinishRows; g++) {
-            const double v = colpart[std::min<int64_t>(g, mtiles - 1) * N + n];  // in bounds, left out past the last
-            s[g] = g < mtiles ? v : 0.0;
+        for (int g = 0; g < 16; g++) s[g] = 0.0;
+        for (int64_t m0 = 0; m0 < mtiles; m0 += 16) {
+#pragma unroll
+            for (int g = 0; g < 16; g++) {
+                const int64_t mt = std::min<int64_t>(m0 + g, mtiles - 1);  // in bounds, left out past the last
+                const double v = colpart[mt * N + n];
+                s[g] += m0 + g < mtiles ? v : 0.0;
+            }
         }
 #pragma unroll
         for (int w = 8; w > 0; w >>= 1)

@@ -425,7 +425,7 @@ hipError_t launch_fwd_small(const void *X, const void *W, const void *Xs, const 
     const uint16_t *y = static_cast<const uint16_t *>(Yref);
     uint16_t *d = static_cast<uint16_t *>(dY);
 #define FS(MSE, MX, WIDE) fwd_small_kernel<MSE, MX, WIDE><<<grid, kThreads, 0, st>>>(X, W, xs, ws, M, N, K, y, d, dscale, colpart, tiles_n, group)
-#define FS_W(MSE, MX) if (wide) FS(MSE, MX, true); else FS(MSE, MX, false)
+#define FS_W(MSE, MX) if (!wide) FS(MSE, MX, false); else FS(MSE, MX, true)
     if (Xs) { if (Yref) { FS_W(true, true); } else { FS_W(false, true); } }
     else { if (Yref) { FS_W(true, false); } else { FS_W(false, false); } }
 #undef FS_W
